@@ -757,33 +757,33 @@ void launch_snapshot(int mi, const CatchDev<T>& C, const int32_t* par, const Cat
     }
 }
 
-// Gauge misfit of the current state, summed over members and gauges into *loss.
+// Gauge misfit of the current state, added to each member's loss: one wavefront
+// per member, summed over the gauges as the row-march form's planner sums them
+// (the same lanes, the same tree), so both forms of the adjoint give the same loss.
 template <typename T, int MI>
-__global__ __launch_bounds__(256) void k_misfit(const CatchDev<T> C, const int32_t* par, int K, const int32_t* grc,
-                                                const double* obs, double* loss) {
+__global__ __launch_bounds__(64) void k_misfit(const CatchDev<T> C, const int32_t* par, int K, const int32_t* grc,
+                                               const double* obs, double* loss_m) {
+    const int m = blockIdx.x;
+    const T* h = C.h[par[C.member_off + m]];
     double acc = 0.0;
-    for (int e = threadIdx.x; e < C.n_members * K; e += 256) {
-        const int m = e / K, k = e % K;
-        const T* h = C.h[par[C.member_off + m]];
+    for (int k = threadIdx.x; k < K; k += 64) {
         const double d = (double)h[state_index<T, MI>(C, m, grc[2 * k], grc[2 * k + 1])] - obs[k];
         acc += d * d;
     }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    __shared__ double part[4];
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) *loss += (part[0] + part[1]) + (part[2] + part[3]);
+    if (threadIdx.x == 0) loss_m[m] += acc;
 }
 
 template <typename T>
 void launch_misfit(int mi, const CatchDev<T>& C, const int32_t* par, int K, const int32_t* grc, const double* obs,
-                   double* loss, hipStream_t s) {
+                   double* loss_m, hipStream_t s) {
     if (K == 0) return;
+    const dim3 grid(C.n_members);
     switch (mi) {
-        case 1: hipLaunchKernelGGL((k_misfit<T, 1>), dim3(1), dim3(256), 0, s, C, par, K, grc, obs, loss); break;
-        case 2: hipLaunchKernelGGL((k_misfit<T, 2>), dim3(1), dim3(256), 0, s, C, par, K, grc, obs, loss); break;
-        case 4: hipLaunchKernelGGL((k_misfit<T, 4>), dim3(1), dim3(256), 0, s, C, par, K, grc, obs, loss); break;
-        default: hipLaunchKernelGGL((k_misfit<T, 8>), dim3(1), dim3(256), 0, s, C, par, K, grc, obs, loss); break;
+        case 1: hipLaunchKernelGGL((k_misfit<T, 1>), grid, dim3(64), 0, s, C, par, K, grc, obs, loss_m); break;
+        case 2: hipLaunchKernelGGL((k_misfit<T, 2>), grid, dim3(64), 0, s, C, par, K, grc, obs, loss_m); break;
+        case 4: hipLaunchKernelGGL((k_misfit<T, 4>), grid, dim3(64), 0, s, C, par, K, grc, obs, loss_m); break;
+        default: hipLaunchKernelGGL((k_misfit<T, 8>), grid, dim3(64), 0, s, C, par, K, grc, obs, loss_m); break;
     }
 }
 

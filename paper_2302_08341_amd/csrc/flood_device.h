@@ -16,6 +16,18 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
+// Workgroup order of a launch: chunk 0 gives each XCD one contiguous range
+// (xcd_remap); chunk n > 0 deals runs of n consecutive workgroups to the XCDs in
+// turn, so that the whole chip works on one stretch of memory and only a run's
+// neighbours share an L2.  The last incomplete round keeps the launch order.
+__device__ __forceinline__ int xcd_order(int b, int nb, int chunk) {
+    if (chunk <= 0) return xcd_remap(b, nb);
+    if (b >= nb / (8 * chunk) * (8 * chunk)) return b;
+    const int x = b & 7, i = b >> 3;
+    const int run = i / chunk;
+    return (run * 8 + x) * chunk + (i - run * chunk);
+}
+
 __device__ __forceinline__ uint32_t to_bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ unsigned long long to_bits(double v) {
     return (unsigned long long)__double_as_longlong(v);
@@ -77,21 +89,41 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // of a cell are half of the hash of (seed, cell pair), so a lane moving
 // adjacent cells hashes once per pair.  In double precision the sum is
 // rounded to nearest.
-template <typename T> __device__ __forceinline__ T depth_add(T h, T inc, uint32_t seed, uint32_t cell);
-template <> __device__ __forceinline__ float depth_add<float>(float h, float inc, uint32_t seed, uint32_t cell) {
+//
+// No test for e == 0 is needed (a product that is not negative is not below it),
+// nor for s == 0 (then e is 0); the comparison u ulp < |e| is made with both
+// sides scaled by 2^16, which rounds the same.
+__device__ __forceinline__ float depth_round(float h, float inc, uint32_t bits16) {
     const float s = h + inc;
     const float bb = s - h;
     const float e = (h - (s - bb)) + (inc - bb);
     const uint32_t sb = __float_as_uint(s);
-    const bool away = (e > 0.0f) == (s > 0.0f);          // toward e: away from zero when e has s's sign
-    const float nb = __uint_as_float(away ? sb + 1u : sb - 1u);
-    const float gap = fabsf(nb - s);
-    const uint32_t r = mix32(seed ^ (cell >> 1)) >> ((cell & 1u) << 4);
-    const float u = (float)(r & 0xffffu) * 0x1p-16f;
-    return (e != 0.0f && s != 0.0f && u * gap < fabsf(e)) ? nb : s;
+    // toward e: one up in magnitude when e has s's sign, else one down
+    const uint32_t step = (uint32_t)((int32_t)(__float_as_uint(e) ^ sb) >> 31) | 1u;
+    const float nb = __uint_as_float(sb + step);
+    return ((float)bits16 * fabsf(nb - s) < fabsf(e) * 65536.0f) ? nb : s;
+}
+template <typename T> __device__ __forceinline__ T depth_add(T h, T inc, uint32_t seed, uint32_t cell);
+template <> __device__ __forceinline__ float depth_add<float>(float h, float inc, uint32_t seed, uint32_t cell) {
+    return depth_round(h, inc, (mix32(seed ^ (cell >> 1)) >> ((cell & 1u) << 4)) & 0xffffu);
 }
 template <> __device__ __forceinline__ double depth_add<double>(double h, double inc, uint32_t, uint32_t) {
     return h + inc;
+}
+// V adjacent cells from an even one on: one hash per pair
+template <typename T, int V>
+__device__ __forceinline__ void depth_add_row(const T (&h)[V], const T (&inc)[V], uint32_t seed, uint32_t cell, T (&out)[V]) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int j = 0; j < V; j += 2) {
+            const uint32_t r = mix32(seed ^ ((cell >> 1) + (uint32_t)(j / 2)));
+            out[j] = depth_round(h[j], inc[j], r & 0xffffu);
+            out[j + 1] = depth_round(h[j + 1], inc[j + 1], r >> 16);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) out[j] = h[j] + inc[j];
+    }
 }
 
 // The adjoint's row-march tape keeps a depth that the step clamped at zero as
@@ -116,17 +148,27 @@ template <typename T> __device__ __forceinline__ T link_depth(T h1, T h2, T dz) 
     return (d >= dz) ? h1 - fmax(dz, T(0)) : h2 - fmax(-dz, T(0));
 }
 
+__device__ __forceinline__ float clamp_between(float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); }
+__device__ __forceinline__ double clamp_between(double v, double lo, double hi) { return fmin(fmax(v, lo), hi); }
+
+// c1, c2: the cells' limiter products h capf; A0 = G s^2 dt.
 template <typename T>
-__device__ __forceinline__ T link_in(T q, T h1, T h2, T dz, T G, const MemberStep<T>& ms, T hdry) {
+__device__ __forceinline__ T link_core(T q, T h1, T h2, T c1, T c2, T dz, T A0, T gdtdx, T hdry) {
     const T d = h1 - h2;
-    const T hf = link_depth(h1, h2, dz);
-    const T num = q - ms.gdtdx * hf * (dz - d);
-    const T A = G * ms.s2dt * pow_m73(hf);
+    const bool up1 = d >= dz;
+    const T hf = (up1 ? h1 : h2) - fmax(up1 ? dz : -dz, T(0));   // link_depth
+    const T num = q - gdtdx * hf * (dz - d);
+    const T A = A0 * pow_m73(hf);
     const T qn = qdiv(num, T(1) + A * fabs(q));
     // donor limiter, branch-free: the lower bound only binds when qn < 0 and the
     // upper bound only when qn > 0 (both bounds straddle zero)
-    const T lim = fmin(fmax(qn, -h2 * ms.capf), h1 * ms.capf);
+    const T lim = clamp_between(qn, -c2, c1);
     return (hf > hdry) ? lim : T(0);
+}
+
+template <typename T>
+__device__ __forceinline__ T link_in(T q, T h1, T h2, T dz, T G, const MemberStep<T>& ms, T hdry) {
+    return link_core(q, h1, h2, h1 * ms.capf, h2 * ms.capf, dz, G * ms.s2dt, ms.gdtdx, hdry);
 }
 
 // Open edge link: outward discharge qo driven by the fixed outward slope Se,
@@ -211,12 +253,37 @@ __device__ __forceinline__ bool march_wave(const CatchDev<T>& C, int local, int 
     return march_wave(C, local, units, k, sx, sy, C.strips_x);
 }
 
-// the cell beside a row-march strip, as loaded by the halo lanes of k_marchv
-template <typename T>
-struct Halo {
-    T h = T(0), z = T(0), n = T(0), q = T(0);   // depth, bed, roughness, east link
-    uint32_t cls = 0;                           // land-cover class (roughness from the member's table)
-};
+// Shifts by one lane across the wavefront (DPP wave_shl:1 / wave_shr:1): lane i
+// takes v of lane i + 1 (lane_shl; lane 63 takes fill) or of lane i - 1
+// (lane_shr; lane 0 takes fill).  Called with the whole wavefront active.
+__device__ __forceinline__ int dpp_shl(int v, int fill) {
+    return __builtin_amdgcn_update_dpp(fill, v, 0x130, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int dpp_shr(int v, int fill) {
+    return __builtin_amdgcn_update_dpp(fill, v, 0x138, 0xf, 0xf, false);
+}
+__device__ __forceinline__ float lane_shl(float v, float fill) {
+    return __int_as_float(dpp_shl(__float_as_int(v), __float_as_int(fill)));
+}
+__device__ __forceinline__ float lane_shr(float v, float fill) {
+    return __int_as_float(dpp_shr(__float_as_int(v), __float_as_int(fill)));
+}
+__device__ __forceinline__ double lane_shl(double v, double fill) {
+    return __hiloint2double(dpp_shl(__double2hiint(v), __double2hiint(fill)),
+                            dpp_shl(__double2loint(v), __double2loint(fill)));
+}
+__device__ __forceinline__ double lane_shr(double v, double fill) {
+    return __hiloint2double(dpp_shr(__double2hiint(v), __double2hiint(fill)),
+                            dpp_shr(__double2loint(v), __double2loint(fill)));
+}
+// v of lane i (wavefront-uniform index) as a wavefront-uniform value
+__device__ __forceinline__ float lane_pick(float v, int i) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+}
+__device__ __forceinline__ double lane_pick(double v, int i) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
+                            __builtin_amdgcn_readlane(__double2loint(v), i));
+}
 
 // v as held by lane src of the wavefront (ds_bpermute: byte address = 4 x lane)
 __device__ __forceinline__ float lane_read(float v, int src) {
@@ -229,11 +296,12 @@ __device__ __forceinline__ double lane_read(double v, int src) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// V adjacent cells moved with one V-wide access (p must be V-element aligned)
+// V adjacent cells moved with one V-wide access; p needs the element's alignment
+// only (global accesses of gfx950 are 4-byte aligned at any width)
 template <typename T, int V> struct VecOf;
-template <> struct VecOf<float, 4> { typedef float __attribute__((ext_vector_type(4))) type; };
-template <> struct VecOf<float, 2> { typedef float __attribute__((ext_vector_type(2))) type; };
-template <> struct VecOf<double, 2> { typedef double __attribute__((ext_vector_type(2))) type; };
+template <> struct VecOf<float, 4> { typedef float __attribute__((ext_vector_type(4), aligned(4))) type; };
+template <> struct VecOf<float, 2> { typedef float __attribute__((ext_vector_type(2), aligned(4))) type; };
+template <> struct VecOf<double, 2> { typedef double __attribute__((ext_vector_type(2), aligned(8))) type; };
 
 template <typename T, int V>
 __device__ __forceinline__ void vload(const T* p, T (&d)[V]) {
@@ -267,5 +335,87 @@ __device__ __forceinline__ void vstore_nt(T* p, const T (&d)[V]) {
     for (int j = 0; j < V; ++j) v[j] = d[j];
     __builtin_nontemporal_store(v, reinterpret_cast<vt*>(p));
 }
+
+// A row array of the march behind a buffer descriptor (four scalar registers).
+// Load addresses are a lane's byte offset vo plus a wavefront-uniform byte offset
+// so; an access past the array's end reads zero or is dropped, so kPastEnd as vo
+// switches a lane off.  The base must be wavefront-uniform.
+constexpr uint32_t kPastEnd = 0xc0000000u;   // arrays are at most 2^31 bytes
+constexpr int kBufNt = 2;                    // cache policy: non-temporal
+
+template <typename T>
+struct Rows {
+    __amdgpu_buffer_rsrc_t rs;
+    const T* p;
+    __device__ __forceinline__ void set(const T* base, uint32_t bytes) {
+        p = base;
+        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)bytes, 0x00020000);
+    }
+    // V cells, 16 or 8 bytes together
+    template <int V, bool NT>
+    __device__ __forceinline__ void load(uint32_t vo, uint32_t so, T (&d)[V]) const {
+        if constexpr (V * sizeof(T) == 16) {
+            typedef unsigned int __attribute__((ext_vector_type(4))) u4;
+            const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, (int)so, NT ? kBufNt : 0);
+            __builtin_memcpy(d, &v, 16);
+        } else {
+            typedef unsigned int __attribute__((ext_vector_type(2))) u2;
+            const u2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)vo, (int)so, NT ? kBufNt : 0);
+            __builtin_memcpy(d, &v, 8);
+        }
+    }
+    // Stores take the whole byte offset in the lane register: after a 128-bit buffer
+    // store with a scalar-register offset, an instruction that overwrote the last
+    // data register in the next slot changed what was stored (lanes 12-15 of each
+    // 16, fourth dword), and the compiler puts the wait state that prevents it only
+    // behind stores whose scalar offset is a constant.
+    template <int V, bool NT>
+    __device__ __forceinline__ void store(uint32_t vo, const T (&d)[V]) const {
+        if constexpr (V * sizeof(T) == 16) {
+            typedef unsigned int __attribute__((ext_vector_type(4))) u4;
+            u4 v;
+            __builtin_memcpy(&v, d, 16);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)vo, 0, NT ? kBufNt : 0);
+        } else {
+            typedef unsigned int __attribute__((ext_vector_type(2))) u2;
+            u2 v;
+            __builtin_memcpy(&v, d, 8);
+            __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)vo, 0, NT ? kBufNt : 0);
+        }
+    }
+    __device__ __forceinline__ T load1(uint32_t vo, uint32_t so) const {
+        T d;
+        if constexpr (sizeof(T) == 4) {
+            const unsigned int v = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)vo, (int)so, 0);
+            __builtin_memcpy(&d, &v, 4);
+        } else {
+            typedef unsigned int __attribute__((ext_vector_type(2))) u2;
+            const u2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)vo, (int)so, 0);
+            __builtin_memcpy(&d, &v, 8);
+        }
+        return d;
+    }
+    __device__ __forceinline__ void store1(uint32_t vo, T d) const {
+        if constexpr (sizeof(T) == 4) {
+            unsigned int v;
+            __builtin_memcpy(&v, &d, 4);
+            __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)vo, 0, 0);
+        } else {
+            typedef unsigned int __attribute__((ext_vector_type(2))) u2;
+            u2 v;
+            __builtin_memcpy(&v, &d, 8);
+            __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)vo, 0, 0);
+        }
+    }
+    __device__ __forceinline__ uint32_t load32(uint32_t vo, uint32_t so) const {
+        return __builtin_amdgcn_raw_buffer_load_b32(rs, (int)vo, (int)so, 0);
+    }
+    __device__ __forceinline__ uint32_t load16(uint32_t vo, uint32_t so) const {
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)vo, (int)so, 0);
+    }
+    __device__ __forceinline__ uint32_t load8(uint32_t vo, uint32_t so) const {
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs, (int)vo, (int)so, 0);
+    }
+};
 
 }  // namespace flood

@@ -97,6 +97,7 @@ template <typename T> struct StepLaunch {
     int32_t total_blocks;
     int32_t n_total;          // members over all catchments
     int32_t recompute;        // 1: adjoint tape recomputation (see k_step)
+    int32_t xcd_chunk;        // workgroup order of the vectorised row march (see xcd_order)
     CatchDev<T> c[kMaxCatch];
     const MemberStep<T>* ms;  // indexed by global member
     typename HBits<T>::type* hbins;  // [kBins][n_total]
@@ -191,7 +192,7 @@ template <typename T> constexpr int march_vec() { return sizeof(T) == 4 ? 4 : 2;
 // with two 85 (5 waves per SIMD), and runs faster.
 template <typename T> constexpr int adj_vec() { return 2; }
 template <typename T>
-void launch_marchv(const StepLaunch<T>& L, int nt, int pf, int ext, int total_waves, hipStream_t s);
+void launch_marchv(const StepLaunch<T>& L, int nt, int ext, int total_waves, hipStream_t s);
 // wavefronts of a row-march launch over one catchment: strips x member units,
 // units padded to a multiple of four in wavefront order 2
 // wavefronts of one row-march launch over a catchment (see march_wave)
@@ -316,7 +317,7 @@ void launch_tape_gather(const CatchDev<T>& tape, const int32_t* blk, const Catch
 void launch_count_group(int G, const double* t, const int32_t* fault, const double* t_end, const int32_t* status,
                         const int32_t* seg_cnt, const int32_t* pool_next, int32_t* out, hipStream_t s);
 template <typename T>
-void launch_marchv_rec(const StepLaunch<T>& L, int pf, int record, int total_waves, hipStream_t s);
+void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s);
 template <typename T>
 void launch_inject(int mi, const CatchDev<T>& after, const int32_t* tags, int K, const int32_t* grc,
                    const double* obs, T* lh, hipStream_t s);
@@ -324,7 +325,7 @@ template <typename T>
 void launch_snapshot(int mi, const CatchDev<T>& C, const int32_t* par, const CatchDev<T>& dst, hipStream_t s);
 template <typename T>
 void launch_misfit(int mi, const CatchDev<T>& C, const int32_t* par, int K, const int32_t* grc,
-                   const double* obs, double* loss, hipStream_t s);
+                   const double* obs, double* loss_m, hipStream_t s);
 void launch_sum_parts(int n_blocks, int n_members, const double* parts, double* out, hipStream_t s);
 
 // particle filter (flood_pf.hip)

@@ -8,6 +8,7 @@
 // shared by two cells is computed by both, identically).
 #include <cfloat>
 #include <cmath>
+#include <type_traits>
 
 #include "flood_device.h"
 
@@ -991,34 +992,79 @@ __global__ __launch_bounds__(kBlock) void k_march(const StepLaunch<T> L) {
 }
 
 // ---------------------------------------------------------------------------
-// Vectorised row-marching step (members in planes, nx a multiple of V): each
-// lane owns V adjacent cells and moves them with one V-wide load or store, so a
-// wavefront streams a strip of 64 V cells per row with five loads and three
-// stores.  Every lane owns cells: the strip starts at a multiple of 64 V cells,
-// so with a row pitch that is a multiple of 16 cells its stores cover whole
-// 64-byte blocks and no block is shared with a neighbouring strip.  The two
-// cells beside the strip come from four single-lane loads per row: lane 0 reads
-// the west neighbour (depth, bed, roughness and its east link) and computes the
-// strip's west link from it exactly as the neighbouring strip computes its
-// east link, lane 63 reads the east neighbour (depth, bed, roughness).  Same
-// link functions and operands as k_step: identical bits.
+// Vectorised row-marching step (members in planes): each lane owns V adjacent
+// cells and moves them with one V-wide load or store, so a wavefront streams a
+// strip of 64 V cells per row.  Every lane owns cells: the strip starts at a
+// multiple of 64 V cells, so with a row pitch that is a multiple of 16 cells its
+// stores cover whole 64-byte blocks and no block is shared with a neighbouring
+// strip.  Where nx is no multiple of V (EXT bit 2) the last lane of a row owns
+// the remainder: it loads V cells all the same (the arrays are padded by V
+// elements) and stores its own one by one.
+//
+// What bounds it is vector issue as much as HBM, so the row loop holds nothing
+// but the links and the depth update of its own cells:
+//  - row addresses are wavefront-uniform bases with one 32-bit lane offset;
+//  - the cells beside the strip are loaded for two rows at a time by lanes 0, 1
+//    (west) and 63, 62 (east), and the strip's west link is evaluated for both
+//    rows at once (exactly as the strip to the west evaluates its last east link:
+//    same operands, same order), as are the domain's west and east edge links.
+//    (A batch of 16 or more rows per evaluation reads the neighbours' cells long
+//    before the neighbours do: 17 % more HBM reads at 2000 x 2000 x 96.);
+//  - the loads of the first row, of the row above the strip, of the cells beside
+//    it and of the second row are all issued before the first is waited for;
+//  - neighbouring lanes' values come by DPP shifts, the halo value entering as
+//    the shift's fill;
+//  - a cell's limiter product h capf serves its four links;
+//  - two rows per loop iteration, so the register sets of the row in work and of
+//    the row in flight swap roles without moves;
+//  - clamped depths, which are rare, are handled under a wavefront-wide test.
+// Same link functions and operands as k_step: identical bits.
+//
+// Measured against the form that kept pointers per stream, evaluated the west
+// link in every row and rotated its registers (160 vector instructions per cell,
+// 72-85 % of the cycles; now about 120): calls of flood_step over 512 x 512 x 16
+// 10.0 -> 8.9 ms, 768 x 1536 x 24 with land cover and running maxima 37.4 ->
+// 31.9 ms, 1024 x 1024 x 16 with inflow links 32.6 -> 26.7 ms, 701 x 503 x 12 (the
+// scalar march before) 8.9 -> 8.1 ms.  2000 x 2000 x 96 stays at 2.0 ms a launch
+// (311 -> 311 ms): there the six state streams of 9.2 GB are at the rate that the
+// same streams reach without arithmetic.
 // ---------------------------------------------------------------------------
-// PF = 1 issues the next row's loads before computing the current row (one row
-// of lookahead), so each wavefront keeps its own loads in flight while it
-// computes.  Loads use a column clamped into the grid and a row clamped to the
-// last row, so no lane needs a branch or a zero fill around them: values of
-// lanes outside the grid and of the row below the last are read but never used.
+// The next row's loads are issued before the current row's arithmetic.  Rows are
+// clamped to the last one: values of the row below it are read but never used.
+// All row traffic goes through buffer descriptors in scalar registers: a lane
+// address is one 32-bit offset in a row plus a wavefront-uniform row offset, and
+// lanes beyond the last column carry an offset past the buffer's end, which the
+// hardware's range check turns into zero loads and dropped stores, so the row
+// loop holds no branch around memory accesses and no address arithmetic, and
+// the compiler's waits leave the next row's loads in flight (as pointers, the
+// addresses of the nine row streams took 18 registers and spilled, and every row
+// waited for all of its loads).
 // REC = 0: the plain step between the member's two state copies.  REC = 1: tape
 // recomputation for the adjoint (tape block ms.blk to block ms.blk_next, a
 // clamped depth stored as -0, no ledger).  REC = 2: the adjoint's recording
 // forward, the same blocks and marks with the plain step's ledger, depth-maximum
-// bins and outflow.
-template <typename T, int V, int NT, int REC, int PF, int EXT>
-__global__ __launch_bounds__(kBlock) void k_marchv(const StepLaunch<T> L) {
+// bins and outflow.  EXT: bit 0 land cover, bit 1 inflow links, bit 2 nx not a
+// multiple of V (neither of the former), bit 3 running maximum.
+constexpr int kMarchLand = 1, kMarchInflow = 2, kMarchRagged = 4, kMarchPeak = 8;
+
+// what a row of a strip needs from memory: its links, and the depth, bed and
+// roughness (land cover: classes) of the row below it
+template <typename T, int V, bool LC, bool PEAK>
+struct MarchRow {
+    T qE[V], qS[V], hs[V], zs[V];
+    T ns[LC ? 1 : V];
+    T pk[PEAK ? V : 1];
+    uint32_t cs;   // land cover: classes of the row below, one byte per cell
+};
+
+template <typename T, int V, int NT, int REC, int EXT>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const StepLaunch<T> L) {
     using HB = typename HBits<T>::type;
+    constexpr bool lc = (EXT & kMarchLand) != 0, INFL = (EXT & kMarchInflow) != 0, RAG = (EXT & kMarchRagged) != 0,
+                   PEAK = (EXT & kMarchPeak) != 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wg = xcd_remap(blockIdx.x, gridDim.x) * (kBlock / 64) + wave;
+    const int wg = xcd_order(blockIdx.x, gridDim.x, L.xcd_chunk) * (kBlock / 64) + wave;
     int ci = 0;
     for (int i = 1; i < L.n_catch; ++i)
         if (wg >= L.c[i].wave_begin) ci = i;
@@ -1032,437 +1078,506 @@ __global__ __launch_bounds__(kBlock) void k_marchv(const StepLaunch<T> L) {
     const int nx = C.nx, ny = C.ny;
     const int x0 = sx * (64 * V);                          // first cell of the strip
     const int xl = x0 + V * lane;                          // first cell of this lane
-    const bool own = xl < nx;                              // nx % V == 0: all V cells or none
+    const bool own = xl < nx;                              // with nx % V == 0 all V cells or none
+    const int tail = RAG ? nx - xl : V;                    // own cells of the lane, if below V
     const bool westw = sx == 0;                            // wavefront-uniform edge tests
     const bool eastw = sx == C.strips_x - 1;
-    const int xa = min(xl, nx - V);                        // load column
-    // halo: lane 0 the cell west of the strip, lane 63 the one east of it
-    // (clamped into the grid where there is none; then never used)
-    const bool halo_lane = lane == 0 || lane == 63;
-    const int xh = lane == 0 ? (westw ? 0 : x0 - 1) : (eastw ? nx - 1 : x0 + 64 * V);
+    const uint32_t es = (uint32_t)sizeof(T);
+    const uint32_t xo = own ? (uint32_t)xl * es : kPastEnd;   // offset in a row, bytes
     const int r0 = sy * C.march_rows;
     const int r1 = min(r0 + C.march_rows, ny);
     const size_t plane = (size_t)ny * nx;
+    const uint32_t pitch = (uint32_t)nx * es;
+    const uint32_t bytes = (uint32_t)plane * es;           // plane <= 2^28 cells
     // source and destination of this member's state: the two copies, or (tape
     // recording and recomputation) the member's tape block and the block of its new state
-    const T* __restrict__ H;
-    const T* __restrict__ QX;
-    const T* __restrict__ QY;
-    T* __restrict__ Ho;
-    T* __restrict__ QXo;
-    T* __restrict__ QYo;
-    const T* QWs;
-    const T* QNs;
-    T* QWo;
-    T* QNo;
+    Rows<T> H, QX, QY, Ho, QXo, QYo;
+    const T *QWs, *QNs;
+    T *QWo, *QNo;
     if constexpr (REC) {
-        const size_t bs = (size_t)ms.blk, bd = (size_t)ms.blk_next;
-        H = C.h[0] + bs * plane;
-        QX = C.qx[0] + bs * plane;
-        QY = C.qy[0] + bs * plane;
-        Ho = C.h[0] + bd * plane;
-        QXo = C.qx[0] + bd * plane;
-        QYo = C.qy[0] + bd * plane;
+        const size_t bs = (size_t)__builtin_amdgcn_readfirstlane(ms.blk);
+        const size_t bd = (size_t)__builtin_amdgcn_readfirstlane(ms.blk_next);
+        H.set(C.h[0] + bs * plane, bytes);
+        QX.set(C.qx[0] + bs * plane, bytes);
+        QY.set(C.qy[0] + bs * plane, bytes);
+        Ho.set(C.h[0] + bd * plane, bytes);
+        QXo.set(C.qx[0] + bd * plane, bytes);
+        QYo.set(C.qy[0] + bd * plane, bytes);
         QWs = C.qw[0] + bs * ny;
         QWo = C.qw[0] + bd * ny;
         QNs = C.qn[0] + bs * nx;
         QNo = C.qn[0] + bd * nx;
     } else {
-        const int sp = ms.parity, dp = sp ^ 1;
-        H = C.h[sp] + (size_t)k * plane;
-        QX = C.qx[sp] + (size_t)k * plane;
-        QY = C.qy[sp] + (size_t)k * plane;
-        Ho = C.h[dp] + (size_t)k * plane;
-        QXo = C.qx[dp] + (size_t)k * plane;
-        QYo = C.qy[dp] + (size_t)k * plane;
-        QWs = C.qw[sp] + (size_t)k * ny;
-        QWo = C.qw[dp] + (size_t)k * ny;
-        QNs = C.qn[sp] + (size_t)k * nx;
-        QNo = C.qn[dp] + (size_t)k * nx;
+        const bool p1 = __builtin_amdgcn_readfirstlane(ms.parity) != 0;
+        const size_t b = (size_t)k * plane;
+        H.set((p1 ? C.h[1] : C.h[0]) + b, bytes);
+        QX.set((p1 ? C.qx[1] : C.qx[0]) + b, bytes);
+        QY.set((p1 ? C.qy[1] : C.qy[0]) + b, bytes);
+        Ho.set((p1 ? C.h[0] : C.h[1]) + b, bytes);
+        QXo.set((p1 ? C.qx[0] : C.qx[1]) + b, bytes);
+        QYo.set((p1 ? C.qy[0] : C.qy[1]) + b, bytes);
+        QWs = (p1 ? C.qw[1] : C.qw[0]) + (size_t)k * ny;
+        QWo = (p1 ? C.qw[0] : C.qw[1]) + (size_t)k * ny;
+        QNs = (p1 ? C.qn[1] : C.qn[0]) + (size_t)k * nx;
+        QNo = (p1 ? C.qn[0] : C.qn[1]) + (size_t)k * nx;
     }
-    const T* __restrict__ Z = C.z;
-    const T* __restrict__ Nn = C.n;
+    Rows<T> Z, NM, PK;
+    Rows<uint8_t> CLS;
+    Z.set(C.z, bytes);
+    if constexpr (lc)
+        CLS.set(C.cls, (uint32_t)plane);
+    else
+        NM.set(C.n, bytes);
+    if constexpr (PEAK) PK.set(C.peak + (size_t)k * plane, bytes);
     const T g = C.g, hdry = C.hdry;
-    const int nb = 2 * (nx + ny);
+    // outflow through open edges (FP64 per member and edge link); inflow links are
+    // not outflow: their volume is logged by the step planner
+    double* acc = C.out_acc + (size_t)k * (2 * (nx + ny));
     // inflow links (edge links with a prescribed inward discharge): the series
     // index of an edge link in the out_acc order, or -1; the series value is
     // picked by a select chain (a per-lane index into the step record would
     // go through private memory)
-    const int8_t* __restrict__ INF = (EXT & 2) ? C.inflow_id : nullptr;
-    auto inflow_q = [&](int id) -> T {
-        T v = ms.qin[0];
-        v = (id == 1) ? ms.qin[1] : v;
-        v = (id == 2) ? ms.qin[2] : v;
-        return (id == 3) ? ms.qin[3] : v;
+    const int8_t* INF = INFL ? C.inflow_id : nullptr;
+    const T qin0 = ms.qin[0], qin1 = ms.qin[1], qin2 = ms.qin[2], qin3 = ms.qin[3];
+    auto inflow_q = [=](int id) -> T {
+        T v = qin0;
+        v = (id == 1) ? qin1 : v;
+        v = (id == 2) ? qin2 : v;
+        return (id == 3) ? qin3 : v;
     };
-    // land cover: the cell's roughness is the member's value for its class, and
-    // its rain is scaled by the class's runoff coefficient
-    const uint8_t* __restrict__ CLS = (EXT & 1) ? C.cls : nullptr;
-    const bool lc = (EXT & 1) && CLS != nullptr;
-    // the member's class table lives in lanes: 0-3 its Manning n of each class,
-    // 4-7 the runoff coefficients, 8-11 the drainage depth of the step for
-    // draining classes (0 for the others); a cell's entries are read from those
-    // lanes with ds_bpermute, a cross-lane read served by the LDS unit, instead
-    // of compare-and-select chains on the VALU.  Every lookup is made where the
-    // whole wavefront is active (the early returns above are wavefront-uniform).
+    // land cover: the member's class table lives in lanes: 0-3 its Manning n of
+    // each class, 4-7 the runoff coefficients, 8-11 the drainage depth of the
+    // step for draining classes (0 for the others); a cell's entries are read
+    // from those lanes with ds_bpermute, a cross-lane read served by the LDS
+    // unit, instead of compare-and-select chains on the VALU.  Every lookup is
+    // made where the whole wavefront is active (the early returns above are
+    // wavefront-uniform).
     T tab = T(0);
-    if (lc) {
-        const int k = lane & 3;
+    if constexpr (lc) {
+        const int c = lane & 3;
         T cn = ms.cn[0], rc = C.class_rc[0];
-        cn = (k == 1) ? ms.cn[1] : cn;
-        cn = (k == 2) ? ms.cn[2] : cn;
-        cn = (k == 3) ? ms.cn[3] : cn;
-        rc = (k == 1) ? C.class_rc[1] : rc;
-        rc = (k == 2) ? C.class_rc[2] : rc;
-        rc = (k == 3) ? C.class_rc[3] : rc;
-        const T dk = ((C.drain_mask >> k) & 1) ? ms.drain : T(0);
+        cn = (c == 1) ? ms.cn[1] : cn;
+        cn = (c == 2) ? ms.cn[2] : cn;
+        cn = (c == 3) ? ms.cn[3] : cn;
+        rc = (c == 1) ? C.class_rc[1] : rc;
+        rc = (c == 2) ? C.class_rc[2] : rc;
+        rc = (c == 3) ? C.class_rc[3] : rc;
+        const T dk = ((C.drain_mask >> c) & 1) ? ms.drain : T(0);
         tab = lane < 4 ? cn : lane < 8 ? rc : lane < 12 ? dk : T(0);
     }
-    auto lut = [&](uint32_t k, int base) -> T { return lane_read(tab, (int)k + base); };
-    auto rough = [&](uint32_t k) -> T { return lut(k, 0); };
-    auto runoff = [&](uint32_t k) -> T { return lut(k, 4); };
-    // roughness of V cells from the shared field, or from their classes (whose
-    // packed bytes are returned in cw)
-    auto load_n = [&](size_t c, T (&nv)[V], uint32_t& cw) {
-        if (lc) {
-            if constexpr (V == 4)
-                cw = *reinterpret_cast<const uint32_t*>(CLS + c);
-            else
-                cw = *reinterpret_cast<const uint16_t*>(CLS + c);
+    auto lut = [&](uint32_t c, int base) -> T { return lane_read(tab, (int)c + base); };
+    auto rough = [&](uint32_t c) -> T { return lut(c, 0); };
+    const uint32_t xc = own ? (uint32_t)xl : kPastEnd;
+    auto classes = [&](uint32_t row) -> uint32_t {   // of the lane's V cells
+        if constexpr (V == 4)
+            return CLS.load32(xc, row);
+        else
+            return CLS.load16(xc, row);
+    };
+    auto rough4 = [&](uint32_t cw, T (&nv)[V]) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) nv[j] = rough((cw >> (8 * j)) & 0xffu);
+        for (int j = 0; j < V; ++j) nv[j] = rough((cw >> (8 * j)) & 0xffu);
+    };
+    // Manning factor g nf^2 of a link, nf = (n1 + n2) / 2 (the halving, exact, is in g4)
+    const T g4 = T(0.25) * g;
+    auto mean_g = [&](T n1, T n2) -> T {
+        const T n = n1 + n2;
+        return g4 * (n * n);
+    };
+    // a lane's own cells of a row; at: the lane's offset in the array
+    auto store_own = [&](auto nt, const Rows<T>& a, uint32_t at, const T (&d)[V]) {
+        if (!RAG || !eastw) {
+            a.template store<V, decltype(nt)::value>(at, d);
         } else {
-            cw = 0;
-            vload<T, V>(Nn + c, nv);
+#pragma unroll
+            for (int j = 0; j < V; ++j) a.store1(j < tail ? at + j * es : kPastEnd, d[j]);
         }
     };
+    constexpr std::integral_constant<bool, NT == 1> nts{};
+    constexpr std::integral_constant<bool, false> cached{};
 
-    size_t ca = (size_t)r0 * nx + xa;
-    T hc[V], zc[V], nc[V], fN[V];
-    uint32_t ccw;
-    vload<T, V>(H + ca, hc);
-    vload<T, V>(Z + ca, zc);
-    load_n(ca, nc, ccw);
-    if (r0 > 0) {
-        T hN[V], zN[V], nN[V], qN[V];
-        uint32_t cwN;
-        vload<T, V>(H + ca - nx, hN);
-        vload<T, V>(Z + ca - nx, zN);
-        load_n(ca - nx, nN, cwN);
-        vload<T, V>(QY + ca - nx, qN);
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const T nf = T(0.5) * (nN[j] + nc[j]);
-            fN[j] = link_in(qN[j], hN[j], hc[j], zc[j] - zN[j], g * (nf * nf), ms, hdry);
+    // Cells beside the strip, for rows r (lanes 0 and 63) and r + 1 (lanes 1 and
+    // 62), and what follows from them: the west link (lanes 0, 1; the domain's west
+    // edge link when westw), the east cell's depth, bed and (land cover) roughness,
+    // or (eastw) the domain's east edge link (lanes 63, 62).
+    struct Beside {
+        T h, z, q, qe, n;
+        uint32_t cls;
+    };
+    Beside hx;
+    T bW = T(0), bN = T(0), bE = T(0), bH = T(0), bZ = T(0);
+    const int cw = westw ? 0 : x0 - 1, ce = eastw ? nx - 1 : x0 + 64 * V;
+    const bool wl = lane < 2, el = lane > 61;
+    const uint32_t hat = wl ? (uint32_t)lane * (uint32_t)nx + (uint32_t)cw
+                            : (uint32_t)(63 - lane) * (uint32_t)nx + (uint32_t)ce;   // cell, from row r
+    const uint32_t hv = (wl || el) ? hat * es : kPastEnd;
+    const uint32_t qv = wl ? (westw ? (uint32_t)lane * es : hv) : kPastEnd;
+    const uint32_t qev = (el && eastw) ? hv : kPastEnd;
+    Rows<T> QH;
+    QH.set(westw ? QWs : QX.p, westw ? (uint32_t)ny * es : bytes);
+    auto beside_load = [&](int r, uint32_t so) {
+        hx.h = H.load1(hv, so);
+        hx.z = Z.load1(hv, so);
+        hx.q = QH.load1(qv, westw ? (uint32_t)r * es : so);
+        hx.qe = QX.load1(qev, so);
+        if constexpr (lc)
+            hx.cls = CLS.load8((wl || el) ? hat : kPastEnd, so / es);
+        else
+            hx.n = NM.load1(hv, so);
+    };
+    // h0, z0, n0: the lane's first cell in row r, h1, z1, n1: in row r + 1
+    auto beside = [&](T h0, T z0, T n0, T h1, T z1, T n1) {
+        T nb = hx.n;
+        if constexpr (lc) nb = rough(hx.cls);
+        bN = nb;
+        // the strip's first cell, row r in lane 0, row r + 1 in lane 1
+        const T hs = lane_shr(h1, h0), zs = lane_shr(z1, z0), n2 = lane_shr(n1, n0);
+        const T hf = lane == 0 ? h0 : hs, zf = lane == 0 ? z0 : zs, nf = lane == 0 ? n0 : n2;
+        if (!westw)
+            bW = link_core(hx.q, hx.h, hf, hx.h * ms.capf, hf * ms.capf, zf - hx.z, mean_g(nb, nf) * ms.s2dt, ms.gdtdx,
+                           hdry);
+        else
+            bW = C.edge_open[3] ? -link_open(-hx.q, hx.h, g * (nb * nb), C.edge_slope[3], ms, hdry) : T(0);
+        bH = hx.h;
+        bZ = hx.z;
+        if (eastw) bE = C.edge_open[1] ? link_open(hx.qe, hx.h, g * (nb * nb), C.edge_slope[1], ms, hdry) : T(0);
+    };
+    // The domain's west and east edge links of the rows passed, lane i those of row
+    // rb + i, written out every 64 rows and at the strip's end.  Inflow links take
+    // their prescribed discharge: the ids of row rb + i are in lane i too.
+    T eW = T(0), eE = T(0);
+    int idW = -1, idE = -1;
+    auto edges_begin = [&](int rb) {
+        if constexpr (INFL) {
+            const int rr = min(rb + lane, ny - 1);
+            idW = (INF && westw) ? (int)INF[2 * nx + rr] : -1;
+            idE = (INF && eastw) ? (int)INF[2 * nx + ny + rr] : -1;
         }
-    } else if (C.edge_open[0]) {
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-            fN[j] = -link_open(-QNs[xa + j], hc[j], g * (nc[j] * nc[j]), C.edge_slope[0], ms, hdry);
-    } else {
-#pragma unroll
-        for (int j = 0; j < V; ++j) fN[j] = T(0);
-    }
+    };
+    auto edges_end = [&](int rb, int re) {
+        const int rr = rb + lane;
+        if (rr >= re) return;
+        if (westw) {
+            QWo[rr] = eW;
+            if (REC != 1 && C.edge_open[3] && idW < 0) acc[2 * nx + rr] += -(double)eW * ms.dxdt;
+        }
+        if (eastw && REC != 1 && C.edge_open[1] && idE < 0) acc[2 * nx + ny + rr] += (double)eE * ms.dxdt;
+    };
+
+    // loads of the row at offset so, and of the row below it
+    auto load_row = [&](uint32_t so, bool below, MarchRow<T, V, lc, PEAK>& m) {
+        const uint32_t sb = below ? so + pitch : so;
+        QX.template load<V, NT == 1>(xo, so, m.qE);
+        QY.template load<V, NT == 1>(xo, so, m.qS);
+        H.template load<V, false>(xo, sb, m.hs);
+        Z.template load<V, false>(xo, sb, m.zs);
+        if constexpr (lc)
+            m.cs = classes(sb / es);
+        else
+            NM.template load<V, false>(xo, sb, m.ns);
+        if constexpr (PEAK) PK.template load<V, false>(xo, so, m.pk);
+    };
+    // first loads, in one go: the strip's first row, the row above it (or the
+    // domain's north edge), the cells beside the strip, the first row's links
+    T hc[V], cc[V], zc[V], nc[V], fN[V];   // row in work: depths, limiter products, bed, (land cover) roughness
+    MarchRow<T, V, lc, PEAK> a, b;
+    a.cs = b.cs = 0;
+    uint32_t ccw = 0;
+    uint32_t so = (uint32_t)r0 * pitch;    // the row in work
+    uint32_t vo = own ? xo + so : kPastEnd;   // this lane's cells in it, for the stores
+    const uint32_t vp = own ? pitch : 0u;
     // inflow ids of the strip's north and south edge links, one byte per cell of
-    // the lane (0xff: none), read before the row loop so that the loop keeps no
-    // table addresses; the west and east ids are read per row, wavefront-uniform
+    // the lane (0xff: none)
     uint32_t nid4 = 0xffffffffu, sid4 = 0xffffffffu;
-    if (INF) {
+    if constexpr (INFL) {
+        if (INF) {
+            const int xa = min(xl, nx - V);   // inflow links need nx % V == 0
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            if (r0 == 0) nid4 = (nid4 & ~(0xffu << (8 * j))) | ((uint32_t)(uint8_t)INF[xa + j] << (8 * j));
-            if (r1 == ny) sid4 = (sid4 & ~(0xffu << (8 * j))) | ((uint32_t)(uint8_t)INF[nx + xa + j] << (8 * j));
+            for (int j = 0; j < V; ++j) {
+                if (r0 == 0) nid4 = (nid4 & ~(0xffu << (8 * j))) | ((uint32_t)(uint8_t)INF[xa + j] << (8 * j));
+                if (r1 == ny) sid4 = (sid4 & ~(0xffu << (8 * j))) | ((uint32_t)(uint8_t)INF[nx + xa + j] << (8 * j));
+            }
         }
     }
     auto id_of = [](uint32_t w, int j) -> int { return (int)(int8_t)(uint8_t)((w >> (8 * j)) & 0xffu); };
-    if (INF && r0 == 0) {
+    {
+        T hN[V], zN[V], qN[V], nN[V];
+        uint32_t cwN = 0;
+        H.template load<V, false>(xo, so, hc);
+        Z.template load<V, false>(xo, so, zc);
+        if constexpr (lc)
+            ccw = classes(so / es);
+        else
+            NM.template load<V, false>(xo, so, nc);
+        Rows<T> qn;
+        qn.set(QNs, pitch);
+        if (r0 > 0) {
+            H.template load<V, false>(xo, so - pitch, hN);
+            Z.template load<V, false>(xo, so - pitch, zN);
+            QY.template load<V, false>(xo, so - pitch, qN);
+            if constexpr (lc)
+                cwN = classes((so - pitch) / es);
+            else
+                NM.template load<V, false>(xo, so - pitch, nN);
+        } else {
+            qn.template load<V, false>(xo, 0, qN);
+        }
+        beside_load(r0, so);
+        load_row(so, r0 + 1 < ny, a);
+        if constexpr (lc) rough4(ccw, nc);
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const int id = id_of(nid4, j);
-            if (id >= 0) fN[j] = inflow_q(id);
+        for (int j = 0; j < V; ++j) cc[j] = hc[j] * ms.capf;
+        if (r0 > 0) {
+            if constexpr (lc) rough4(cwN, nN);
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+                fN[j] = link_core(qN[j], hN[j], hc[j], hN[j] * ms.capf, cc[j], zc[j] - zN[j], mean_g(nN[j], nc[j]) * ms.s2dt,
+                                  ms.gdtdx, hdry);
+        } else {
+            // north edge of the domain: the links, their strip and the outflow through them
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                fN[j] = T(0);
+                if (C.edge_open[0]) fN[j] = -link_open(-qN[j], hc[j], g * (nc[j] * nc[j]), C.edge_slope[0], ms, hdry);
+                if constexpr (INFL) {
+                    const int id = id_of(nid4, j);
+                    if (id >= 0) fN[j] = inflow_q(id);
+                }
+            }
+            Rows<T> qno;
+            qno.set(QNo, pitch);
+            store_own(cached, qno, xo, fN);
+            if (own && REC != 1 && C.edge_open[0]) {
+#pragma unroll
+                for (int j = 0; j < V; ++j)
+                    if ((!RAG || j < tail) && id_of(nid4, j) < 0) acc[xl + j] += -(double)fN[j] * ms.dxdt;
+            }
         }
     }
-    // current row's links (qE, qS), the row below (hs, zs, ns, classes csw) and
-    // the current row's halo cell (depth, bed, roughness or class, east link)
-    T hs[V], zs[V], ns[V], qE[V], qS[V];
-    uint32_t csw = 0;
-    Halo<T> hx;
-    auto load_row = [&](size_t c, bool below, T (&qe)[V], T (&qs)[V], T (&h2)[V], T (&z2)[V], T (&n2)[V],
-                        uint32_t& cw2, Halo<T>& ho) {
-        const size_t cb = below ? c + nx : c;
-        if (NT) {
-            vload_nt<T, V>(QX + c, qe);
-            vload_nt<T, V>(QY + c, qs);
-        } else {
-            vload<T, V>(QX + c, qe);
-            vload<T, V>(QY + c, qs);
-        }
-        vload<T, V>(H + cb, h2);
-        vload<T, V>(Z + cb, z2);
-        load_n(cb, n2, cw2);
-        if (halo_lane) {
-            const size_t c1 = c - xa + xh;
-            ho.h = H[c1];
-            ho.z = Z[c1];
-            ho.q = QX[c1];
-            if (lc)
-                ho.cls = CLS[c1];
-            else
-                ho.n = Nn[c1];
-        }
-    };
-    // roughness of the halo cell from its class: a cross-lane read, made with the
-    // whole wavefront active
-    auto halo_n = [&](const Halo<T>& ho) -> T { return lc ? rough(halo_lane ? ho.cls : 0u) : ho.n; };
-    if (PF) load_row(ca, r0 + 1 < ny, qE, qS, hs, zs, ns, csw, hx);
-    // PF == 2: a second row in flight (the links of the next row and the state
-    // of the row after it), so each row's loads have two rows of work to arrive
-    T hsB[V], zsB[V], nsB[V], qEB[V], qSB[V];
-    uint32_t cswB = 0;
-    Halo<T> hxB;
-#pragma unroll
-    for (int j = 0; j < V; ++j) hsB[j] = zsB[j] = nsB[j] = qEB[j] = qSB[j] = T(0);
-    if (PF == 2 && r0 + 1 < r1) load_row(ca + nx, r0 + 2 < ny, qEB, qSB, hsB, zsB, nsB, cswB, hxB);
+
     HB vmax = 0;
-    T vcl = T(0);
-    T vdr = T(0);
-    for (int r = r0; r < r1; ++r) {
-        const bool hasS = r + 1 < ny;
-        const int idW = (INF && westw) ? (int)INF[2 * nx + r] : -1;
-        const int idE = (INF && eastw) ? (int)INF[2 * nx + ny + r] : -1;
-        T hs2[V], zs2[V], ns2[V], qE2[V], qS2[V];
-        uint32_t csw2 = 0;
-        Halo<T> hx2;
-        if (PF == 2) {
-            if (r + 2 < r1) load_row(ca + 2 * (size_t)nx, r + 3 < ny, qE2, qS2, hs2, zs2, ns2, csw2, hx2);
-        } else if (PF) {
-            if (r + 1 < r1) load_row(ca + nx, r + 2 < ny, qE2, qS2, hs2, zs2, ns2, csw2, hx2);
+    T vcl = T(0), vdr = T(0);
+    double vdrain = 0.0;
+    uint32_t cell = (uint32_t)r0 * (uint32_t)nx + (uint32_t)xl;
+    // one row: m holds its loads, nxt takes those of the next row; odd: the second
+    // row of a pair; bi: the row's lane in the edge registers
+    auto row = [&](int r, auto odd, int bi, MarchRow<T, V, lc, PEAK>& m, MarchRow<T, V, lc, PEAK>& nxt) {
+        constexpr int o = decltype(odd)::value;
+        load_row(r + 1 < r1 ? so + pitch : so, r + 2 < ny, nxt);
+        T ns[V];
+        if constexpr (lc) {
+            rough4(m.cs, ns);
         } else {
-            load_row(ca, hasS, qE, qS, hs, zs, ns, csw, hx);
+#pragma unroll
+            for (int j = 0; j < V; ++j) ns[j] = m.ns[j];
         }
-        const T nH = halo_n(hx);
-        // east neighbour of the lane's last cell = first cell of the next lane; for
-        // lane 63 the halo cell east of the strip
-        T hE = __shfl_down(hc[0], 1, 64);
-        T zE = __shfl_down(zc[0], 1, 64);
-        T nE = __shfl_down(nc[0], 1, 64);
-        if (lane == 63) {
-            hE = hx.h;
-            zE = hx.z;
-            nE = nH;
+        if constexpr (o == 0) {
+            beside(hc[0], zc[0], nc[0], m.hs[0], m.zs[0], ns[0]);
+            beside_load(r + 2, so + 2 * pitch);
         }
-        T fE[V];
+        // east neighbour of the lane's last cell = first cell of the next lane, lane 63's the halo cell
+        const T hE = lane_shl(hc[0], lane_pick(bH, 63 - o));
+        const T zE = lane_shl(zc[0], lane_pick(bZ, 63 - o));
+        const T nE = lane_shl(nc[0], lane_pick(bN, 63 - o));
+        T fE[V], fS[V], fW[V], cs[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const T h2 = (j + 1 < V) ? hc[j + 1] : hE;
             const T z2 = (j + 1 < V) ? zc[j + 1] : zE;
-            const T n2 = (j + 1 < V) ? nc[j + 1] : nE;
-            const T nf = T(0.5) * (nc[j] + n2);
-            fE[j] = link_in(qE[j], hc[j], h2, z2 - zc[j], g * (nf * nf), ms, hdry);
+            const T c2 = (j + 1 < V) ? cc[j + 1] : hE * ms.capf;
+            const T G = mean_g(nc[j], (j + 1 < V) ? nc[j + 1] : nE);
+            fE[j] = link_core(m.qE[j], hc[j], h2, cc[j], c2, z2 - zc[j], G * ms.s2dt, ms.gdtdx, hdry);
         }
+        T w = lane_pick(bW, o);
         if (eastw) {
+            T e = lane_pick(bE, 63 - o);
+            if constexpr (INFL) {
+                const int id = __builtin_amdgcn_readlane(idE, bi);
+                if (id >= 0) e = -inflow_q(id);
+            }
 #pragma unroll
-            for (int j = 0; j < V; ++j)
-                if (xl + j + 1 == nx) {
-                    fE[j] = C.edge_open[1] ? link_open(qE[j], hc[j], g * (nc[j] * nc[j]), C.edge_slope[1], ms, hdry)
-                                           : T(0);
-                    if (idE >= 0) fE[j] = -inflow_q(idE);
-                }
+            for (int j = RAG ? 0 : V - 1; j < V; ++j) fE[j] = (xl + j + 1 == nx) ? e : fE[j];
+            eE = lane == bi ? e : eE;
         }
-        T fW[V];
-        fW[0] = __shfl_up(fE[V - 1], 1, 64);
-        if (lane == 0 && !westw) {
-            // the strip's west link, as the strip to the west computes it (its last
-            // cell's east link: same operands in the same order)
-            const T nf = T(0.5) * (nH + nc[0]);
-            fW[0] = link_in(hx.q, hx.h, hc[0], zc[0] - hx.z, g * (nf * nf), ms, hdry);
+        if (westw) {
+            if constexpr (INFL) {
+                const int id = __builtin_amdgcn_readlane(idW, bi);
+                if (id >= 0) w = inflow_q(id);
+            }
+            eW = lane == bi ? w : eW;
         }
+        fW[0] = lane_shr(fE[V - 1], w);
 #pragma unroll
         for (int j = 1; j < V; ++j) fW[j] = fE[j - 1];
-        if (westw && xl == 0) {
-            fW[0] = C.edge_open[3] ? -link_open(-QWs[r], hc[0], g * (nc[0] * nc[0]), C.edge_slope[3], ms, hdry)
-                                   : T(0);
-            if (idW >= 0) fW[0] = inflow_q(idW);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            cs[j] = m.hs[j] * ms.capf;
+            fS[j] = link_core(m.qS[j], hc[j], m.hs[j], cc[j], cs[j], m.zs[j] - zc[j], mean_g(nc[j], ns[j]) * ms.s2dt,
+                              ms.gdtdx, hdry);
         }
-        T fS[V];
-        if (hasS) {
+        if (r + 1 == ny) {
+            // south edge of the domain
 #pragma unroll
             for (int j = 0; j < V; ++j) {
-                const T nf = T(0.5) * (nc[j] + ns[j]);
-                fS[j] = link_in(qS[j], hc[j], hs[j], zs[j] - zc[j], g * (nf * nf), ms, hdry);
-            }
-        } else {
-            if (C.edge_open[2]) {
-#pragma unroll
-                for (int j = 0; j < V; ++j)
-                    fS[j] = link_open(qS[j], hc[j], g * (nc[j] * nc[j]), C.edge_slope[2], ms, hdry);
-            } else {
-#pragma unroll
-                for (int j = 0; j < V; ++j) fS[j] = T(0);
-            }
-            if (INF) {
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
+                fS[j] = T(0);
+                if (C.edge_open[2])
+                    fS[j] = link_open(m.qS[j], hc[j], g * (nc[j] * nc[j]), C.edge_slope[2], ms, hdry);
+                if constexpr (INFL) {
                     const int id = id_of(sid4, j);
                     if (id >= 0) fS[j] = -inflow_q(id);
                 }
             }
         }
-        T hn4[V];
-        bool cf[V];
+        T hn[V], inc[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const T dv = ((fW[j] - fE[j]) + fN[j]) - fS[j];
-            const uint32_t kc = (ccw >> (8 * j)) & 0xffu;
-            const T rn = lc ? ms.rinc * runoff(kc) : ms.rinc;
-            T hn = depth_add(hc[j], ms.dtdx * dv + rn, ms.seed, (uint32_t)(r * nx + xl + j));
-            cf[j] = hn < T(0);
-            vcl += (own && hn < T(0)) ? -hn : T(0);
-            hn = (hn < T(0)) ? T(0) : hn;
-            // drainage of draining classes, up to the water the cell holds
-            const T loss = lc ? fmin(lut(kc, 8), hn) : T(0);
-            hn = hn - loss;
-            vdr += own ? loss : T(0);
-            hn = (hn == T(0)) ? T(0) : hn;
-            hn4[j] = hn;
-            const HB hb = to_bits(hn);
-            vmax = (own && hb > vmax) ? hb : vmax;
+            T rn = ms.rinc;
+            if constexpr (lc) rn = ms.rinc * lut((ccw >> (8 * j)) & 0xffu, 4);
+            inc[j] = ms.dtdx * dv + rn;
         }
-        if (own) {
-            // the tape keeps a clamped depth as -0 (the clamp branch for the adjoint)
-            T ho4[V];
+        if constexpr (RAG) {
+            // the first cell of the lane may be odd, so a pair's hash may serve two lanes
 #pragma unroll
-            for (int j = 0; j < V; ++j) ho4[j] = (REC && cf[j]) ? -T(0) : hn4[j];
-            if (NT) {
-                vstore_nt<T, V>(Ho + ca, ho4);
-                vstore_nt<T, V>(QXo + ca, fE);
-                vstore_nt<T, V>(QYo + ca, fS);
-            } else {
-                vstore<T, V>(Ho + ca, ho4);
-                vstore<T, V>(QXo + ca, fE);
-                vstore<T, V>(QYo + ca, fS);
-            }
-            if constexpr (REC != 1) {
-                if (C.peak) {
-                    T* PK = C.peak + (size_t)k * plane + ca;
-                    T pk4[V];
-                    vload<T, V>(PK, pk4);
+            for (int j = 0; j < V; ++j) hn[j] = depth_add(hc[j], inc[j], ms.seed, cell + (uint32_t)j);
+            if (eastw) {
 #pragma unroll
-                    for (int j = 0; j < V; ++j) pk4[j] = fmax(pk4[j], hn4[j]);
-                    vstore<T, V>(PK, pk4);
-                }
+                for (int j = 0; j < V; ++j) hn[j] = j < tail ? hn[j] : T(0);
             }
-            if (westw && xl == 0) QWo[r] = fW[0];
-            if (r == 0) {
+        } else {
+            depth_add_row<T, V>(hc, inc, ms.seed, cell, hn);
+        }
+        bool neg[V];
+        bool any = false;
 #pragma unroll
-                for (int j = 0; j < V; ++j) QNo[xl + j] = fN[j];
-            }
-            // outflow through open edges (FP64 per member and edge link)
-            if (REC != 1 && (westw || eastw || r == 0 || !hasS)) {
-                double* acc = C.out_acc + (size_t)k * nb;
-                // inflow links are not outflow: their volume is logged by the step planner
+        for (int j = 0; j < V; ++j) {
+            neg[j] = hn[j] < T(0);
+            any |= neg[j];
+        }
+        if (__any(any)) {
 #pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    const int x = xl + j;
-                    if (r == 0 && C.edge_open[0] && id_of(nid4, j) < 0) acc[x] += -(double)fN[j] * ms.dxdt;
-                    if (!hasS && C.edge_open[2] && id_of(sid4, j) < 0) acc[nx + x] += (double)fS[j] * ms.dxdt;
-                    if (x == 0 && C.edge_open[3] && idW < 0) acc[2 * nx + r] += -(double)fW[j] * ms.dxdt;
-                    if (x + 1 == nx && C.edge_open[1] && idE < 0) acc[2 * nx + ny + r] += (double)fE[j] * ms.dxdt;
-                }
+            for (int j = 0; j < V; ++j) {
+                vcl += neg[j] ? -hn[j] : T(0);
+                // the tape keeps a clamped depth as -0 (the clamp branch for the adjoint)
+                hn[j] = neg[j] ? (REC ? -T(0) : T(0)) : hn[j];
             }
+        }
+        if constexpr (lc) {
+            // drainage of draining classes, up to the water the cell holds; summed per
+            // eight rows of the grid, so that the sum is the same for every strip height
+            // that is a multiple of eight
+            if ((r & 7) == 0) {
+                vdrain += (double)vdr;
+                vdr = T(0);
+            }
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const T loss = fmin(lut((ccw >> (8 * j)) & 0xffu, 8), hn[j]);
+                hn[j] = hn[j] - loss;
+                vdr += loss;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            // -0 (tape marks only) must not enter the bit-pattern maximum
+            const HB hb = REC ? to_bits(hn[j] + T(0)) : to_bits(hn[j]);
+            vmax = hb > vmax ? hb : vmax;
+        }
+        store_own(nts, Ho, vo, hn);
+        store_own(nts, QXo, vo, fE);
+        store_own(nts, QYo, vo, fS);
+        if constexpr (PEAK) {
+            T pk[V];
+#pragma unroll
+            for (int j = 0; j < V; ++j) pk[j] = fmax(m.pk[j], REC ? hn[j] + T(0) : hn[j]);
+            store_own(cached, PK, vo, pk);
         }
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             fN[j] = fS[j];
-            hc[j] = hs[j];
-            zc[j] = zs[j];
+            hc[j] = m.hs[j];
+            zc[j] = m.zs[j];
+            cc[j] = cs[j];
             nc[j] = ns[j];
         }
-        ccw = csw;
-        if (PF == 2) {
-            csw = cswB;
-            cswB = csw2;
-            hx = hxB;
-            hxB = hx2;
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                qE[j] = qEB[j];
-                qS[j] = qSB[j];
-                hs[j] = hsB[j];
-                zs[j] = zsB[j];
-                ns[j] = nsB[j];
-                qEB[j] = qE2[j];
-                qSB[j] = qS2[j];
-                hsB[j] = hs2[j];
-                zsB[j] = zs2[j];
-                nsB[j] = ns2[j];
-            }
-        } else if (PF) {
-            csw = csw2;
-            hx = hx2;
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                qE[j] = qE2[j];
-                qS[j] = qS2[j];
-                hs[j] = hs2[j];
-                zs[j] = zs2[j];
-                ns[j] = ns2[j];
-            }
+        ccw = m.cs;
+        so += pitch;
+        vo += vp;
+        cell += (uint32_t)nx;
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    for (int rb = r0; rb < r1; rb += 64) {
+        const int re = min(rb + 64, r1);
+        edges_begin(rb);
+        int r = rb;
+        for (; r + 1 < re; r += 2) {
+            row(r, even, r - rb, a, b);
+            row(r + 1, odd, r + 1 - rb, b, a);
         }
-        ca += nx;
+        if (r < re) row(r, even, r - rb, a, b);   // the strip's last row (64 rows end even)
+        if (westw || eastw) edges_end(rb, re);
+    }
+    if (REC != 1 && r1 == ny && C.edge_open[2] && own) {
+#pragma unroll
+        for (int j = 0; j < V; ++j)
+            if ((!RAG || j < tail) && id_of(sid4, j) < 0) acc[nx + xl + j] += (double)fN[j] * ms.dxdt;
     }
     if constexpr (REC != 1) {
+        // lanes beyond the last column hold no cells
+        vmax = own ? vmax : HB(0);
         for (int off = 32; off > 0; off >>= 1) {
             const HB o = __shfl_xor(vmax, off, 64);
             vmax = o > vmax ? o : vmax;
         }
-        double cl = (double)vcl;
-        for (int off = 32; off > 0; off >>= 1) cl += __shfl_xor(cl, off, 64);
-        if (lc) {
-            double dr = (double)vdr;
+        if constexpr (lc) {
+            double dr = own ? vdrain + (double)vdr : 0.0;
             for (int off = 32; off > 0; off >>= 1) dr += __shfl_xor(dr, off, 64);
             // spread over kBins accumulators per member: the wavefronts in flight
             // mostly belong to one member, so a single address would serialise them
             if (lane == 0 && dr != 0.0)
                 atomicAdd(C.drain_acc + (size_t)k * kBins + (blockIdx.x & (kBins - 1)), dr * (C.dx * C.dx));
         }
-        if (lane == 0) {
-            if (vmax != 0) {
-                HB* a = L.hbins + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + C.member_off + k;
-                const HB cur = __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (vmax > cur) atomicMax(a, vmax);
-            }
-            if (cl != 0.0) atomicAdd(&L.vclamp[C.member_off + k], cl * (C.dx * C.dx));
+        vcl = own ? vcl : T(0);
+        if (__any(vcl != T(0))) {
+            double cl = (double)vcl;
+            for (int off = 32; off > 0; off >>= 1) cl += __shfl_xor(cl, off, 64);
+            if (lane == 0) atomicAdd(&L.vclamp[C.member_off + k], cl * (C.dx * C.dx));
+        }
+        if (lane == 0 && vmax != 0) {
+            HB* bin = L.hbins + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + C.member_off + k;
+            const HB cur = __hip_atomic_load(bin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (vmax > cur) atomicMax(bin, vmax);
         }
     }
 }
 
+// ext: kMarch* bits; an instantiation carries only the code of the extensions it
+// names, so the plain step keeps its register budget
 template <typename T, int EXT>
-static void launch_marchv_ext(const StepLaunch<T>& L, int nt, int pf, const dim3 grid, hipStream_t s) {
+static void launch_marchv_ext(const StepLaunch<T>& L, int nt, const dim3 grid, hipStream_t s) {
     constexpr int V = march_vec<T>();
-    if (nt && pf == 2)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, 2, EXT>), grid, dim3(kBlock), 0, s, L);
-    else if (nt && pf)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, 1, EXT>), grid, dim3(kBlock), 0, s, L);
-    else if (nt)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, 0, EXT>), grid, dim3(kBlock), 0, s, L);
-    else if (pf)
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, 1, EXT>), grid, dim3(kBlock), 0, s, L);
+    if (nt)
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, EXT>), grid, dim3(kBlock), 0, s, L);
     else
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, 0, EXT>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, EXT>), grid, dim3(kBlock), 0, s, L);
 }
 
-// ext: bit 0 land cover, bit 1 inflow links; an instantiation carries only the
-// code of the extensions it names, so the plain step keeps its register budget
 template <typename T>
-void launch_marchv(const StepLaunch<T>& L, int nt, int pf, int ext, int total_waves, hipStream_t s) {
+void launch_marchv(const StepLaunch<T>& L, int nt, int ext, int total_waves, hipStream_t s) {
     const int per = kBlock / 64;
     const dim3 grid((total_waves + per - 1) / per);
-    switch (ext & 3) {
-        case 0: launch_marchv_ext<T, 0>(L, nt, pf, grid, s); break;
-        case 1: launch_marchv_ext<T, 1>(L, nt, pf, grid, s); break;
-        case 2: launch_marchv_ext<T, 2>(L, nt, pf, grid, s); break;
-        default: launch_marchv_ext<T, 3>(L, nt, pf, grid, s); break;
+    switch (ext) {
+        case 0: launch_marchv_ext<T, 0>(L, nt, grid, s); break;
+        case 1: launch_marchv_ext<T, 1>(L, nt, grid, s); break;
+        case 2: launch_marchv_ext<T, 2>(L, nt, grid, s); break;
+        case 3: launch_marchv_ext<T, 3>(L, nt, grid, s); break;
+        case 4: launch_marchv_ext<T, 4>(L, nt, grid, s); break;
+        case 8: launch_marchv_ext<T, 8>(L, nt, grid, s); break;
+        case 9: launch_marchv_ext<T, 9>(L, nt, grid, s); break;
+        case 10: launch_marchv_ext<T, 10>(L, nt, grid, s); break;
+        case 11: launch_marchv_ext<T, 11>(L, nt, grid, s); break;
+        default: launch_marchv_ext<T, 12>(L, nt, grid, s); break;
     }
 }
 
@@ -1473,26 +1588,22 @@ void launch_marchv(const StepLaunch<T>& L, int nt, int pf, int ext, int total_wa
 // marks, plus everything the plain step
 // updates (depth maximum bins, clamp and outflow ledgers, running maximum).
 template <typename T>
-void launch_marchv_rec(const StepLaunch<T>& L, int pf, int record, int total_waves, hipStream_t s) {
+void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s) {
     const int per = kBlock / 64;
     const dim3 grid((total_waves + per - 1) / per);
     constexpr int V = march_vec<T>();
-    if (record) {
-        if (pf)
-            hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 1, 0>), grid, dim3(kBlock), 0, s, L);
-        else
-            hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 0, 0>), grid, dim3(kBlock), 0, s, L);
-    } else if (pf) {
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 1, 0>), grid, dim3(kBlock), 0, s, L);
-    } else {
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 0, 0>), grid, dim3(kBlock), 0, s, L);
-    }
+    if (record && L.c[0].peak)
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, kMarchPeak>), grid, dim3(kBlock), 0, s, L);
+    else if (record)
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 0>), grid, dim3(kBlock), 0, s, L);
+    else
+        hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 0>), grid, dim3(kBlock), 0, s, L);
 }
 
-template void launch_marchv<float>(const StepLaunch<float>&, int, int, int, int, hipStream_t);
-template void launch_marchv<double>(const StepLaunch<double>&, int, int, int, int, hipStream_t);
-template void launch_marchv_rec<float>(const StepLaunch<float>&, int, int, int, hipStream_t);
-template void launch_marchv_rec<double>(const StepLaunch<double>&, int, int, int, hipStream_t);
+template void launch_marchv<float>(const StepLaunch<float>&, int, int, int, hipStream_t);
+template void launch_marchv<double>(const StepLaunch<double>&, int, int, int, hipStream_t);
+template void launch_marchv_rec<float>(const StepLaunch<float>&, int, int, hipStream_t);
+template void launch_marchv_rec<double>(const StepLaunch<double>&, int, int, hipStream_t);
 
 template <typename T> void launch_march(const StepLaunch<T>& L, int seg, int total_waves, hipStream_t s) {
     const int per = kBlock / 64;

@@ -73,7 +73,8 @@ template <typename T> struct Impl : ImplBase {
     int forced_order = -1;    // >= 0: the only order the tuner tries
     int march_bands = 0;      // order 4: bands of rows of strips (multiple of 8); 0: from the L2 size
     int march_nt = 1;         // non-temporal state streams in the vectorised row-marching kernel
-    int march_pf = 1;         // one row of load lookahead in the vectorised row-marching kernel
+    bool nt_forced = false;
+    int march_xcd = 0;        // workgroup order of the vectorised row-marching kernel (see xcd_order)
     int adj_pf = 0;           // the same in the adjoint's reverse march (off: 4.64 s against 4.15 s per C5 call)
     int total_waves = 0;      // waves of one row-marching launch
     int n_catch = 0, n_total = 0;
@@ -349,7 +350,18 @@ template <typename T> struct Impl : ImplBase {
             SL.c[i] = d;
         }
         SL.total_blocks = begin;
+        SL.xcd_chunk = march_xcd;
         total_waves = waves;
+        if (!nt_forced) {
+            // What a step reads and writes: where it fits the 256 MB last-level cache,
+            // plain accesses leave the new state there for the next step (1024 x 1024 x 8,
+            // 202 MB: 51 us a step against 57 us; 512 x 512 x 16: 34 against 39 us); beyond
+            // it, accesses marked non-temporal are the faster ones (1024 x 1024 x 16, 403 MB:
+            // 101 against 106 us; 2000 x 2000 x 96: 2.07 against 2.19 ms)
+            double moved = 0.0;
+            for (const Cat& c : cats) moved += (double)c.ny * c.nx * (6.0 * c.N + 2.0) * sizeof(T);
+            march_nt = moved > 230e6 ? 1 : 0;
+        }
         SL.ms = ms;
         SL.hbins = hbins;
         SL.vclamp = vclamp;
@@ -357,7 +369,9 @@ template <typename T> struct Impl : ImplBase {
 
     void launch_steps(const StepLaunch<T>& L) {
         if (variant == 3 && !L.recompute)
-            launch_marchv<T>(L, march_nt, march_pf, (any_land ? 1 : 0) | (any_inflow ? 2 : 0), total_waves, st);
+            launch_marchv<T>(L, march_nt,
+                             (any_land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() ? 0 : 4) | (L.c[0].peak ? 8 : 0),
+                             total_waves, st);
         else if (variant == 2 && !L.recompute)
             launch_march<T>(L, march_seg, total_waves, st);
         else
@@ -396,8 +410,11 @@ template <typename T> struct Impl : ImplBase {
             march_order = std::min(4, std::max(0, std::atoi(mo)));
             forced_order = march_order;
         }
-        if (const char* nt = std::getenv("FLOOD_MARCH_NT")) march_nt = std::atoi(nt) ? 1 : 0;
-        if (const char* pf = std::getenv("FLOOD_MARCH_PF")) march_pf = std::min(2, std::max(0, std::atoi(pf)));
+        if (const char* nt = std::getenv("FLOOD_MARCH_NT")) {
+            march_nt = std::atoi(nt) ? 1 : 0;
+            nt_forced = true;
+        }
+        if (const char* xc = std::getenv("FLOOD_MARCH_XCD")) march_xcd = std::min(4096, std::max(0, std::atoi(xc)));
         if (const char* pf = std::getenv("FLOOD_ADJ_PF")) adj_pf = std::atoi(pf) ? 1 : 0;
         const char* ng = std::getenv("FLOOD_NO_GRAPH");
         use_graph = !(ng && ng[0] == '1');
@@ -441,13 +458,12 @@ template <typename T> struct Impl : ImplBase {
         mi = ch.mi;
         variant = params[0].step_kernel ? params[0].step_kernel : ch.variant;
         march_seg = params[0].march_members ? params[0].march_members : ch.march_seg;
-        if (variant == 3 && !vector_ok()) {
-            if (params[0].step_kernel == 3) {
-                err = "the vectorised kernel needs member_interleave 1 and nx a multiple of " +
-                      std::to_string(march_vec<T>());
-                return FLOOD_EINVAL;
-            }
-            variant = 2;
+        // asked for by number, the vectorised kernel needs whole vectors in every row;
+        // chosen by the library it takes any row length
+        if (params[0].step_kernel == 3 && !vector_ok()) {
+            err = "the vectorised kernel needs member_interleave 1 and nx a multiple of " +
+                  std::to_string(march_vec<T>());
+            return FLOOD_EINVAL;
         }
         if (mi != 1) variant = 1;
         // land cover runs on the vectorised row-march kernel only (per-member class
@@ -821,9 +837,18 @@ template <typename T> struct Impl : ImplBase {
             int variant, rows, cpb, mrows, seg, order;
         };
         std::vector<Cand> cands;
-        const bool want1 = !vector_only() && (params[0].step_kernel == 0 || params[0].step_kernel == 1 || mi != 1);
-        const bool want2 = !vector_only() && mi == 1 && (params[0].step_kernel == 0 || params[0].step_kernel == 2);
-        const bool want3 = vector_ok() && (params[0].step_kernel == 0 || params[0].step_kernel == 3);
+        // Left to itself the library steps members in planes with the vectorised row
+        // march, of any row length.  The tiled kernel serves interleaved members and
+        // competes where a launch holds few cells: it reads a cell's neighbours at once
+        // where the march goes row by row (128 x 128 cells in FP64: 8.4 us against 12;
+        // from about 130,000 cells on the march was the faster one in every trial).  The
+        // scalar march serves whoever asks for it by number.
+        size_t cells = 0;
+        for (const Cat& c : cats) cells += (size_t)c.ny * c.nx * c.N;
+        const bool want1 = !vector_only() && (params[0].step_kernel == 1 || mi != 1 ||
+                                              (params[0].step_kernel == 0 && cells <= (size_t)1 << 17));
+        const bool want2 = !vector_only() && mi == 1 && params[0].step_kernel == 2;
+        const bool want3 = mi == 1 && (params[0].step_kernel == 0 || params[0].step_kernel == 3);
         if (want1)
             for (int r : {1, 2, 4, 8})
                 for (int cp : cpbs)
@@ -840,10 +865,15 @@ template <typename T> struct Impl : ImplBase {
                     for (int mr : {8, 16, 32, 64, 128})
                         cands.push_back({2, cats[0].tile_rows, cats[0].cpb, mr, sg, od});
         }
-        if (want3)
+        if (want3) {
+            // strips of 2 rows pay where a launch has too few wavefronts for the chip
+            // otherwise; with land cover heights are multiples of eight rows, the blocks
+            // that the drained volume is summed by
+            const std::vector<int> heights = any_land ? std::vector<int>{8, 16, 32, 64} : std::vector<int>{2, 4, 8, 16, 32, 64};
             for (int od : {0, 1, 2, 3, 4})
                 if (forced_order < 0 || od == forced_order)
-                    for (int mr : {4, 8, 16, 32, 64}) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od});
+                    for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od});
+        }
         Cand bc = cands.empty()
                       ? Cand{variant, cats[0].tile_rows, cats[0].cpb, cats[0].march_rows, march_seg, march_order}
                       : cands[0];
@@ -933,7 +963,8 @@ template <typename T> struct Impl : ImplBase {
         // refined in turn (the others held), timing the whole batched launch; a
         // change is kept only when it is more than 1 % faster
         if (n_catch > 1 && variant >= 2) {
-            const std::vector<int> rows_set = variant == 3 ? std::vector<int>{4, 8, 16, 32, 64}
+            const std::vector<int> rows_set = any_land       ? std::vector<int>{8, 16, 32, 64}
+                                              : variant == 3 ? std::vector<int>{4, 8, 16, 32, 64}
                                                            : std::vector<int>{8, 16, 32, 64, 128};
             auto time_layout = [&](float* out) -> flood_status {
                 layout_launch();
@@ -1830,7 +1861,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
     // members in planes with a vectorisable row length: the adjoint runs in
     // row-march form (forward, tape recomputation and reverse step), otherwise
     // in the tiled form that also serves interleaved members
-    const bool march_adj = mi == 1 && variant == 3;
+    const bool march_adj = variant == 3 && vector_ok();
     size_t env_group = 0;
     if (const char* eg = std::getenv("FLOOD_ADJ_GROUP")) {   // testing: force smaller member groups
         const long v = std::atol(eg);
@@ -1960,14 +1991,14 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
     double *d_obs2 = nullptr, *d_loss = nullptr, *d_nbar = nullptr, *d_mubar = nullptr, *d_gm = nullptr;
     CHK(talloc(2 * std::max(K, 1) * sizeof(int32_t), (void**)&d_grc2));
     CHK(talloc((size_t)S * std::max(K, 1) * sizeof(double), (void**)&d_obs2));
-    CHK(talloc(sizeof(double), (void**)&d_loss));
+    CHK(talloc((size_t)N * sizeof(double), (void**)&d_loss));   // tiled form: misfit per member
     CHK(talloc(ncell * sizeof(double), (void**)&d_nbar));
     CHK(talloc((size_t)N * sizeof(double), (void**)&d_gm));
     if (K > 0) {
         HIPCHK(hipMemcpyAsync(d_grc2, grc, 2 * K * sizeof(int32_t), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(d_obs2, obs, (size_t)S * K * sizeof(double), hipMemcpyHostToDevice, st));
     }
-    HIPCHK(hipMemsetAsync(d_loss, 0, sizeof(double), st));
+    HIPCHK(hipMemsetAsync(d_loss, 0, (size_t)N * sizeof(double), st));
     HIPCHK(hipMemsetAsync(d_nbar, 0, ncell * sizeof(double), st));
     // Tape.  Row-march form: the pool of blocks, each field's blocks contiguous
     // (block b of the depth at b * ncell, of the west edge strip at b * ny, ...),
@@ -2016,8 +2047,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
     size_t rec_cap = 0;
     int32_t* seg_n = nullptr;
     size_t segn_cap = 0;
-    double loss_host = 0.0;
-    std::vector<double> loss_slot(N, 0.0);   // each slot's misfit (row-march form)
+    std::vector<double> loss_slot(N, 0.0);   // each slot's misfit
     if (march_adj) {
         CHK(talloc((size_t)Gi * sizeof(int32_t), (void**)&d_lpar));
         CHK(talloc((size_t)Gi * sizeof(int32_t), (void**)&d_segcnt));
@@ -2270,7 +2300,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             auto launch_fwd_batch = [&](int slot) -> flood_status {
                 for (int i = 0; i < B; ++i) {
                     launch_plan<T>(PLg, st);
-                    launch_marchv_rec<T>(RF, march_pf, 1, tw, st);
+                    launch_marchv_rec<T>(RF, 1, tw, st);
                 }
                 L += B;
                 launch_count_group(Gg, t + off + g0, fault + off + g0, d_tend, status, d_segcnt, d_pool,
@@ -2401,7 +2431,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
                         R.c[0] = TVR;
                         R.ms = recs + (size_t)r * Gi - (off + g0);
                         R.clamp_out = nullptr;
-                        launch_marchv_rec<T>(R, march_pf, 0, tw, st);
+                        launch_marchv_rec<T>(R, 0, tw, st);
                     }
                 }
                 launch_adj_segment<T>(Gg, Gi, sg == last_seg ? nullptr : nseg + Gi, nseg, recs,
@@ -2489,7 +2519,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
                     return FLOOD_ESTATE;
                 }
             }
-            launch_misfit<T>(mi, V, par, K, d_grc2, d_obs2 + (size_t)smp * K, d_loss, st);
+            launch_misfit<T>(mi, V, par, K, d_grc2, d_obs2 + (size_t)smp * K, d_loss + g0, st);
         }
         std::vector<int32_t> any_h(L);
         HIPCHK(hipMemcpyAsync(any_h.data(), any_log, L * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -2562,13 +2592,12 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(st));
     }
-    double loss_h = 0.0;
-    HIPCHK(hipMemcpyAsync(&loss_h, d_loss, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    if (march_adj) {
-        for (int m = 0; m < N; ++m) loss_host += loss_slot[inv[m]];   // member order
-        loss_h = loss_host;
+    if (!march_adj) {
+        HIPCHK(hipMemcpyAsync(loss_slot.data(), d_loss, (size_t)N * sizeof(double), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
     }
+    double loss_h = 0.0;
+    for (int m = 0; m < N; ++m) loss_h += loss_slot[inv[m]];   // member order
     last_adj_groups = groups_run;
     last_adj_group_size = group_most;
     last_adj_segments = n_segments;

@@ -1,0 +1,80 @@
+"""Vectorised row march at the edges of its strips, lanes and batches.
+
+The tiled kernel (step_kernel 1) evaluates the same link functions per cell and is
+held to the oracle elsewhere; every path of the row march must give its bits.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+RAIN = np.array([130.0, 60.0]) * 1e-3 / 3600.0
+
+
+@pytest.fixture(scope="module")
+def fl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2302_08341_amd import flood
+    flood.load_library()
+    return flood
+
+
+def _catch(ny, nx, n_members, edges=(1, 1, 1, 1), seed=11):
+    rng = np.random.default_rng(seed)
+    dem = (0.02 * rng.uniform(0.0, 1.0, (ny, nx)) + 0.01 * np.arange(ny)[:, None]).astype(np.float32)
+    return dict(dem=dem, manning=rng.uniform(0.02, 0.05, (ny, nx)).astype(np.float32), dx=3.0, edge_kind=edges,
+                edge_slope=tuple(1e-3 * e for e in edges), n_members=n_members, n_scale=rng.uniform(0.8, 1.2, n_members),
+                rain_mult=rng.uniform(0.5, 1.5, n_members), h0=rng.uniform(0.0, 0.3, (ny, nx)).astype(np.float32))
+
+
+def _same(fl, cat, t_end, **kw):
+    a = fl.FloodEnsemble([cat], RAIN, member_interleave=1, step_kernel=1, track_peak=True, real_bytes=kw["real_bytes"])
+    b = fl.FloodEnsemble([cat], RAIN, member_interleave=1, track_peak=True, **kw)
+    a.step(t_end)
+    b.step(t_end)
+    assert b.config()["step_kernel"] == 3
+    for m in range(cat["n_members"]):
+        for w in (fl.FIELD_H, fl.FIELD_QX, fl.FIELD_QY, fl.FIELD_PEAK):
+            np.testing.assert_array_equal(a.field(m, w), b.field(m, w))
+    la, lb = a.ledger(), b.ledger()
+    for k in ("rain_in", "t", "steps"):
+        np.testing.assert_array_equal(la[k], lb[k])
+    for k in ("outflow", "storage"):     # FP64 sums in another order
+        np.testing.assert_allclose(la[k], lb[k], rtol=1e-12)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+@pytest.mark.parametrize("ny,nx,rows", [(5, 1, 2), (3, 3, 64), (70, 255, 7), (130, 257, 100), (66, 259, 64), (131, 130, 65)])
+def test_rows_of_any_length(fl, monkeypatch, rb, ny, nx, rows):
+    # without the tuner a handle that names no kernel takes the row march, whatever its row length
+    monkeypatch.setenv("FLOOD_AUTOTUNE", "0")
+    _same(fl, _catch(ny, nx, 2), 20.0, real_bytes=rb, march_rows=rows)
+
+
+@pytest.mark.parametrize("edges", [(1, 0, 0, 1), (0, 1, 1, 0)])
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 129])
+def test_tall_strips_and_edges(fl, edges, rows):
+    # the domain's west and east edge links are kept for 64 rows at a time
+    _same(fl, _catch(130, 512, 2, edges), 15.0, real_bytes=4, step_kernel=3, march_rows=rows)
+
+
+def test_stores_under_load(fl):
+    # 1024 columns x 1024 rows x 4 members: enough waves in flight that a store's data
+    # register can still be unread when the next instruction issues; the adjoint's recording
+    # forward writes blocks that nothing else rewrites
+    c = W.urban_catchment("march", 1024, 1024, 4, 123, n_gauges=4)
+    cat = dict(dem=c.dem, manning=c.manning, dx=c.dx, edge_kind=c.edge_kind, edge_slope=c.edge_slope, n_members=4,
+               n_scale=c.n_scale, rain_mult=c.rain_mult)
+    ens = [fl.FloodEnsemble([cat], RAIN, step_kernel=sk) for sk in (1, 3)]
+    loss = []
+    for e in ens:
+        e.step(50.0)
+        loss.append(e.adjoint(0, 60.0, 10.0, c.gauges, np.full((1, 4), 0.05), 100)[0])
+    assert loss[0] == loss[1]
+    for m in range(4):
+        for w in (fl.FIELD_H, fl.FIELD_QX, fl.FIELD_QY):
+            np.testing.assert_array_equal(ens[0].field(m, w), ens[1].field(m, w))
