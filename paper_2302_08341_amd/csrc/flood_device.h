@@ -276,6 +276,37 @@ __device__ __forceinline__ double lane_shr(double v, double fill) {
     return __hiloint2double(dpp_shr(__double2hiint(v), __double2hiint(fill)),
                             dpp_shr(__double2loint(v), __double2loint(fill)));
 }
+// value i of four (0 for i outside 1..3)
+template <typename T> __device__ __forceinline__ T pick4(int i, T a, T b, T c, T d) {
+    T v = a;
+    v = (i == 1) ? b : v;
+    v = (i == 2) ? c : v;
+    return (i == 3) ? d : v;
+}
+// maximum over the wavefront, in every lane's scalar view (DPP row shifts and row
+// broadcasts, the total in lane 63)
+__device__ __forceinline__ uint32_t wave_max_bits(uint32_t v) {
+#define FLOOD_DPP_MAX(ctrl, rows)                                                                  \
+    {                                                                                              \
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false); \
+        v = o > v ? o : v;                                                                         \
+    }
+    FLOOD_DPP_MAX(0x111, 0xf)   // row_shr:1
+    FLOOD_DPP_MAX(0x112, 0xf)   // row_shr:2
+    FLOOD_DPP_MAX(0x114, 0xf)   // row_shr:4
+    FLOOD_DPP_MAX(0x118, 0xf)   // row_shr:8
+    FLOOD_DPP_MAX(0x142, 0xa)   // row_bcast:15
+    FLOOD_DPP_MAX(0x143, 0xc)   // row_bcast:31
+#undef FLOOD_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max_bits(unsigned long long v) {
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v, off, 64);
+        v = o > v ? o : v;
+    }
+    return v;
+}
 // v of lane i (wavefront-uniform index) as a wavefront-uniform value
 __device__ __forceinline__ float lane_pick(float v, int i) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));

@@ -92,6 +92,30 @@ template <typename T> struct CatchDev {
     const int8_t* inflow_id;
 };
 
+struct PlanCatch;
+
+// Planning inside the step (k_marchv): what k_plan reads and writes, with the
+// arrays that every wavefront of a member reads in two copies (depth-maximum
+// bins in four): launch i of a batch reads copy i & 1 (bins i & 3) and its
+// member's first wavefront writes the other (the step's maxima go to bins
+// i + 1 & 3, and bins i + 2 & 3 are cleared for the launch after), so no launch
+// writes what its wavefronts read.  Batches are multiples of four launches and
+// start and end with the current values in the first copies.
+template <typename T> struct StepPlan {
+    using HB = typename HBits<T>::type;
+    const PlanCatch* pc;      // [n_catch], device memory; null: planned by k_plan
+    const double* t_end;      // device scalar
+    const double *t_in, *s, *mu, *clsn, *drain;
+    const int64_t *steps_in, *lim;
+    const int32_t *par_in, *fault_in;
+    const HB* bins_in;
+    HB *bins_out, *bins_clear;
+    double *t_out, *vrain, *vin, *dt_last, *dtlog, *telog;
+    int64_t *steps_out, *log_n;
+    int32_t *par_out, *fault_out, *status;
+    int32_t dtlog_cap;
+};
+
 template <typename T> struct StepLaunch {
     int32_t n_catch;
     int32_t total_blocks;
@@ -103,6 +127,7 @@ template <typename T> struct StepLaunch {
     typename HBits<T>::type* hbins;  // [kBins][n_total]
     double* vclamp;           // [n_total]
     uint8_t* clamp_out;       // tiled recompute only: 1 where the new depth was clamped at zero
+    StepPlan<T> plan;
     // tape recording and recomputation by the row-march kernel: c[0]'s copy-0
     // arrays are the tape's block pools (block b of a field at b times the member
     // stride); a member reads block ms.blk and writes block ms.blk_next, a
@@ -141,6 +166,7 @@ template <typename T> struct PlanLaunch {
     double* telog;            // optional [n_total][dtlog_cap] step end times
     int64_t* log_n;           // [n_total] steps logged since the log was opened (may exceed dtlog_cap)
     int32_t dtlog_cap;
+    double* dt_last;          // [n_total] length of each member's last step
     const int64_t* step_lim;  // optional [n_total]: a member whose step count has reached it does not step
     int32_t m_begin, m_end;   // members planned by this launch (global indices)
     // adjoint record of this launch (null when not recording), indexed by m - m_begin
@@ -201,9 +227,12 @@ inline int march_waves(int strips_x, int strips_y, int units, int order, int ban
     if (order == 4) return strips_x * ((strips_y + bands - 1) / bands * bands) * units;
     return strips_x * strips_y * units;
 }
-// members still short of t_end (and, when lim is given, of their step limit)
+// out[0]: members still short of t_end (and, when lim is given, of their step
+// limit), out[1]: the status word, and, when dt is given (each member's last step
+// length), out[2]: the steps that the member furthest behind still needs at that
+// length
 void launch_count_active(int n_total, const double* t, const int32_t* fault, const double* t_end,
-                         const int32_t* status, const int64_t* steps, const int64_t* lim, int32_t* out,
+                         const int32_t* status, const int64_t* steps, const int64_t* lim, const double* dt, int32_t* out,
                          hipStream_t s);
 // lim[m] = steps[m] + n for the n_total members (n < 0: no limit)
 void launch_step_limit(int n_total, const int64_t* steps, int64_t n, int64_t* lim, hipStream_t s);

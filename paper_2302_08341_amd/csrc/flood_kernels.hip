@@ -197,6 +197,7 @@ __global__ __launch_bounds__(256) void k_plan(const PlanLaunch<T> P) {
         P.log_n[m] = li + 1;
     }
     P.t[m] = tn;
+    P.dt_last[m] = dt;
     P.par[m] = ms.parity ^ 1;
     P.steps[m] = st + 1;
     P.vrain[m] += (double)ms.rinc * C.ncells * (C.dx * C.dx);
@@ -401,25 +402,41 @@ template <typename T> void launch_step_mi(int mi, const StepLaunch<T>& L, hipStr
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_count_active(int n, const double* t, const int32_t* fault,
                                                       const double* t_end, const int32_t* status,
-                                                      const int64_t* steps, const int64_t* lim, int32_t* out) {
-    __shared__ int part[4];
-    int c = 0;
+                                                      const int64_t* steps, const int64_t* lim, const double* dt,
+                                                      int32_t* out) {
+    __shared__ int part[4], mpart[4];
+    int c = 0, need = 0;
     const double te = *t_end;
-    for (int m = threadIdx.x; m < n; m += 256)
-        c += (!fault[m] && t[m] < te && (!lim || steps[m] < lim[m])) ? 1 : 0;
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    for (int m = threadIdx.x; m < n; m += 256) {
+        if (fault[m] || !(t[m] < te) || (lim && steps[m] >= lim[m])) continue;
+        ++c;
+        if (dt) {
+            // an estimate: the step length follows the depth and shortens before block edges
+            double k = dt[m] > 0.0 ? ceil((te - t[m]) / dt[m]) : 1.0;
+            if (lim && (double)(lim[m] - steps[m]) < k) k = (double)(lim[m] - steps[m]);
+            need = max(need, (int)fmin(k, 1e9));
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        c += __shfl_xor(c, off, 64);
+        need = max(need, __shfl_xor(need, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[threadIdx.x >> 6] = c;
+        mpart[threadIdx.x >> 6] = need;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         out[0] = part[0] + part[1] + part[2] + part[3];
         out[1] = status[0];
+        if (dt) out[2] = max(max(mpart[0], mpart[1]), max(mpart[2], mpart[3]));
     }
 }
 
 void launch_count_active(int n_total, const double* t, const int32_t* fault, const double* t_end,
-                         const int32_t* status, const int64_t* steps, const int64_t* lim, int32_t* out,
+                         const int32_t* status, const int64_t* steps, const int64_t* lim, const double* dt, int32_t* out,
                          hipStream_t s) {
-    hipLaunchKernelGGL(k_count_active, dim3(1), dim3(256), 0, s, n_total, t, fault, t_end, status, steps, lim, out);
+    hipLaunchKernelGGL(k_count_active, dim3(1), dim3(256), 0, s, n_total, t, fault, t_end, status, steps, lim, dt, out);
 }
 
 __global__ __launch_bounds__(256) void k_count_group(int n, const double* t, const int32_t* fault,
@@ -1057,8 +1074,149 @@ struct MarchRow {
     uint32_t cs;   // land cover: classes of the row below, one byte per cell
 };
 
-template <typename T, int V, int NT, int REC, int EXT>
-__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const StepLaunch<T> L) {
+// The step planned by the wavefronts that take it: each of a member's wavefronts
+// folds the member's depth-maximum bins and forms the step's coefficients itself,
+// in the same operations as k_plan, while its first rows are on their way; the
+// member's first wavefront (lead) writes the member's new clock, ledger and log.
+// A planner launch before every step costs its 4-7 us and a launch gap of 4 us
+// (a third to a half of a step of 512 x 512 x 16 cells and less); folded in, the
+// bins' reduction and one division for three quotients cost a wavefront about
+// 300 cycles.
+template <typename T> struct PlanHead {
+    using HB = typename HBits<T>::type;
+    double t, t_end;
+    int64_t steps;
+    int32_t par;
+    HB hb;          // depth-maximum bin of this lane
+};
+
+// the member's clock; false (and, by the lead wavefront, the member's values
+// carried over to the next launch) when it takes no step
+template <typename T>
+__device__ __forceinline__ bool plan_head(const StepPlan<T>& P, int m, int n_total, int lane, bool lead, PlanHead<T>& h) {
+    h.t = P.t_in[m];
+    h.t_end = *P.t_end;
+    h.steps = P.steps_in[m];
+    h.par = P.par_in[m];
+    h.hb = P.bins_in[(size_t)lane * n_total + m];
+    const int fault = P.fault_in[m];
+    if (!fault && h.t < h.t_end && h.steps < P.lim[m]) return true;
+    if (lead) {
+        P.bins_out[(size_t)lane * n_total + m] = h.hb;
+        P.bins_clear[(size_t)lane * n_total + m] = 0;
+        if (lane == 0) {
+            P.t_out[m] = h.t;
+            P.steps_out[m] = h.steps;
+            P.par_out[m] = h.par;
+            P.fault_out[m] = fault;
+        }
+    }
+    return false;
+}
+
+// the step's coefficients; false when the member is frozen (see k_plan)
+template <typename T>
+__device__ __forceinline__ bool plan_step(const StepPlan<T>& P, const PlanCatch& C, int m, int n_total, int lane, bool lead,
+                                          const PlanHead<T>& h, MemberStep<T>& ms) {
+    const T H = from_bits<T>(wave_max_bits(h.hb));
+    const double t = h.t;
+    const double jf = floor(t / C.rain_interval);
+    const bool rains = jf >= 0.0 && jf < (double)C.n_rain;
+    const double R = rains ? C.rain[(int64_t)jf] : 0.0;
+    double dt;
+    if (C.dt_fixed > 0.0) {
+        dt = C.dt_fixed;
+    } else {
+        double Hd = (double)H;
+        if (Hd < C.hdry) Hd = C.hdry;
+        dt = C.alpha * C.dx / sqrt(C.g * Hd);
+        if (dt > C.dt_cap) dt = C.dt_cap;
+    }
+    const double edge = (jf + 1.0 > (double)C.n_rain) ? INFINITY : (jf + 1.0) * C.rain_interval;
+    const double tev = h.t_end < edge ? h.t_end : edge;
+    double tn;
+    if (dt >= tev - t) {
+        dt = tev - t;
+        tn = tev;
+    } else {
+        tn = t + dt;
+    }
+    const bool finite = H <= (sizeof(T) == 4 ? T(FLT_MAX) : T(DBL_MAX));
+    if (!finite || !(tn > t)) {
+        if (lead) {
+            P.bins_out[(size_t)lane * n_total + m] = h.hb;
+            P.bins_clear[(size_t)lane * n_total + m] = 0;
+            if (lane == 0) {
+                P.fault_out[m] = 1;
+                atomicOr(P.status, 1);
+                P.t_out[m] = t;
+                P.steps_out[m] = h.steps;
+                P.par_out[m] = h.par;
+            }
+        }
+        return false;
+    }
+    // dt / dx, g dt / dx and dx / (4 dt), one division in three lanes
+    const double num = lane == 0 ? dt : lane == 1 ? C.g * dt : C.dx;
+    const double den = lane == 2 ? 4.0 * dt : C.dx;
+    const T quo = (T)(num / den);
+    const double sc = P.s[m], mu = P.mu[m];
+    ms.dtdx = lane_pick(quo, 0);
+    ms.gdtdx = lane_pick(quo, 1);
+    ms.capf = lane_pick(quo, 2);
+    ms.gdt = lane_pick((T)(C.g * dt), 0);
+    ms.s2dt = lane_pick((T)(sc * sc * dt), 0);
+    ms.rinc = lane_pick((T)(mu * R * dt), 0);
+    ms.dxdt = C.dx * dt;
+    ms.active = 1;
+    ms.parity = h.par;
+    ms.slot = ms.blk = ms.blk_next = -1;
+    const uint64_t tb = (uint64_t)__double_as_longlong(t);
+    ms.seed = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)mix32((uint32_t)tb ^ mix32((uint32_t)(tb >> 32) + 0x632be5abu)));
+    for (int k = 0; k < kMaxClasses; ++k) ms.cn[k] = P.clsn ? (T)P.clsn[(size_t)m * kMaxClasses + k] : T(0);
+    ms.drain = P.drain ? lane_pick((T)(P.drain[m] * dt), 0) : T(0);
+    double vq = 0.0;
+#pragma unroll
+    for (int j = 0; j < kMaxSeries; ++j) {
+        ms.qin[j] = T(0);
+        if (j < C.n_series) {
+            const double q = rains ? C.inflow_q[(size_t)j * C.n_rain + (int64_t)jf] : 0.0;
+            ms.qin[j] = lane_pick((T)q, 0);
+            vq += C.wq[j] * q;
+        }
+    }
+    if (lead) {
+        P.bins_clear[(size_t)lane * n_total + m] = 0;
+        if (lane == 0) {
+            P.t_out[m] = tn;
+            P.steps_out[m] = h.steps + 1;
+            P.par_out[m] = h.par ^ 1;
+            P.fault_out[m] = 0;
+            P.dt_last[m] = dt;
+            if (C.n_series > 0) P.vin[m] += vq * dt;
+            P.vrain[m] += (double)ms.rinc * C.ncells * (C.dx * C.dx);
+            if (P.dtlog) {
+                const int64_t li = P.log_n[m];
+                if (li < P.dtlog_cap) {
+                    P.dtlog[(size_t)m * P.dtlog_cap + li] = dt;
+                    P.telog[(size_t)m * P.dtlog_cap + li] = tn;
+                }
+                P.log_n[m] = li + 1;
+            }
+        }
+    }
+    return true;
+}
+
+// PLAN: the step is planned here (REC = 0), else by k_plan into L.ms.
+// Wavefronts per SIMD the registers are budgeted for: four in FP32 (128 registers; three
+// where inflow links meet another extension and four would spill), two in FP64.
+template <typename T> constexpr int march_occupancy(int ext) {
+    return sizeof(T) == 8 ? 2 : ((ext & kMarchInflow) && (ext & ~kMarchInflow)) ? 3 : 4;
+}
+template <typename T, int V, int NT, int REC, int EXT, bool PLAN>
+__global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(const StepLaunch<T> L) {
     using HB = typename HBits<T>::type;
     constexpr bool lc = (EXT & kMarchLand) != 0, INFL = (EXT & kMarchInflow) != 0, RAG = (EXT & kMarchRagged) != 0,
                    PEAK = (EXT & kMarchPeak) != 0;
@@ -1073,8 +1231,17 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
     if (local >= C.n_waves) return;
     int k, sx, sy;
     if (!march_wave(C, local, C.n_members, k, sx, sy)) return;
-    const MemberStep<T> ms = L.ms[C.member_off + k];
-    if (!ms.active) return;
+    const int mg = C.member_off + k;
+    const bool lead = sx == 0 && sy == 0;
+    MemberStep<T> ms;
+    PlanHead<T> head;
+    if constexpr (PLAN) {
+        if (!plan_head<T>(L.plan, mg, L.n_total, lane, lead, head)) return;
+        ms.parity = head.par;
+    } else {
+        ms = L.ms[mg];
+        if (!ms.active) return;
+    }
     const int nx = C.nx, ny = C.ny;
     const int x0 = sx * (64 * V);                          // first cell of the strip
     const int xl = x0 + V * lane;                          // first cell of this lane
@@ -1138,13 +1305,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
     // picked by a select chain (a per-lane index into the step record would
     // go through private memory)
     const int8_t* INF = INFL ? C.inflow_id : nullptr;
-    const T qin0 = ms.qin[0], qin1 = ms.qin[1], qin2 = ms.qin[2], qin3 = ms.qin[3];
-    auto inflow_q = [=](int id) -> T {
-        T v = qin0;
-        v = (id == 1) ? qin1 : v;
-        v = (id == 2) ? qin2 : v;
-        return (id == 3) ? qin3 : v;
-    };
+    auto inflow_q = [&](int id) -> T { return pick4(id, ms.qin[0], ms.qin[1], ms.qin[2], ms.qin[3]); };
     // land cover: the member's class table lives in lanes: 0-3 its Manning n of
     // each class, 4-7 the runoff coefficients, 8-11 the drainage depth of the
     // step for draining classes (0 for the others); a cell's entries are read
@@ -1153,18 +1314,6 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
     // made where the whole wavefront is active (the early returns above are
     // wavefront-uniform).
     T tab = T(0);
-    if constexpr (lc) {
-        const int c = lane & 3;
-        T cn = ms.cn[0], rc = C.class_rc[0];
-        cn = (c == 1) ? ms.cn[1] : cn;
-        cn = (c == 2) ? ms.cn[2] : cn;
-        cn = (c == 3) ? ms.cn[3] : cn;
-        rc = (c == 1) ? C.class_rc[1] : rc;
-        rc = (c == 2) ? C.class_rc[2] : rc;
-        rc = (c == 3) ? C.class_rc[3] : rc;
-        const T dk = ((C.drain_mask >> c) & 1) ? ms.drain : T(0);
-        tab = lane < 4 ? cn : lane < 8 ? rc : lane < 12 ? dk : T(0);
-    }
     auto lut = [&](uint32_t c, int base) -> T { return lane_read(tab, (int)c + base); };
     auto rough = [&](uint32_t c) -> T { return lut(c, 0); };
     const uint32_t xc = own ? (uint32_t)xl : kPastEnd;
@@ -1324,6 +1473,21 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
         }
         beside_load(r0, so);
         load_row(so, r0 + 1 < ny, a);
+        if constexpr (PLAN) {
+            if (!plan_step<T>(L.plan, L.plan.pc[ci], mg, L.n_total, lane, lead, head, ms)) return;
+        }
+        if constexpr (lc) {
+            const int c = lane & 3;
+            T cn = ms.cn[0], rc = C.class_rc[0];
+            cn = (c == 1) ? ms.cn[1] : cn;
+            cn = (c == 2) ? ms.cn[2] : cn;
+            cn = (c == 3) ? ms.cn[3] : cn;
+            rc = (c == 1) ? C.class_rc[1] : rc;
+            rc = (c == 2) ? C.class_rc[2] : rc;
+            rc = (c == 3) ? C.class_rc[3] : rc;
+            const T dk = ((C.drain_mask >> c) & 1) ? ms.drain : T(0);
+            tab = lane < 4 ? cn : lane < 8 ? rc : lane < 12 ? dk : T(0);
+        }
         if constexpr (lc) rough4(ccw, nc);
 #pragma unroll
         for (int j = 0; j < V; ++j) cc[j] = hc[j] * ms.capf;
@@ -1542,10 +1706,10 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
         if (__any(vcl != T(0))) {
             double cl = (double)vcl;
             for (int off = 32; off > 0; off >>= 1) cl += __shfl_xor(cl, off, 64);
-            if (lane == 0) atomicAdd(&L.vclamp[C.member_off + k], cl * (C.dx * C.dx));
+            if (lane == 0) atomicAdd(&L.vclamp[mg], cl * (C.dx * C.dx));
         }
         if (lane == 0 && vmax != 0) {
-            HB* bin = L.hbins + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + C.member_off + k;
+            HB* bin = (PLAN ? L.plan.bins_out : L.hbins) + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + mg;
             const HB cur = __hip_atomic_load(bin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (vmax > cur) atomicMax(bin, vmax);
         }
@@ -1557,10 +1721,15 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_marchv(const
 template <typename T, int EXT>
 static void launch_marchv_ext(const StepLaunch<T>& L, int nt, const dim3 grid, hipStream_t s) {
     constexpr int V = march_vec<T>();
-    if (nt)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, EXT>), grid, dim3(kBlock), 0, s, L);
+    static_assert(sizeof(StepLaunch<T>) <= 4096, "kernel arguments");
+    if (L.plan.pc && nt)
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, EXT, true>), grid, dim3(kBlock), 0, s, L);
+    else if (L.plan.pc)
+        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, EXT, true>), grid, dim3(kBlock), 0, s, L);
+    else if (nt)
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 0, EXT, false>), grid, dim3(kBlock), 0, s, L);
     else
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, EXT>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, 0, 0, EXT, false>), grid, dim3(kBlock), 0, s, L);
 }
 
 template <typename T>
@@ -1593,11 +1762,11 @@ void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipS
     const dim3 grid((total_waves + per - 1) / per);
     constexpr int V = march_vec<T>();
     if (record && L.c[0].peak)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, kMarchPeak>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, kMarchPeak, false>), grid, dim3(kBlock), 0, s, L);
     else if (record)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 0>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 0, false>), grid, dim3(kBlock), 0, s, L);
     else
-        hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 0>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 0, false>), grid, dim3(kBlock), 0, s, L);
 }
 
 template void launch_marchv<float>(const StepLaunch<float>&, int, int, int, hipStream_t);

@@ -101,7 +101,8 @@ template <typename T> struct Impl : ImplBase {
     double* d_tend = nullptr;
     int32_t* d_count = nullptr;
     double* h_tend = nullptr;      // pinned
-    int32_t* h_count = nullptr;    // pinned [2 slots][2]
+    int32_t* h_count = nullptr;    // pinned [2 slots][4]: a batch's counts
+    int32_t* d_hcount = nullptr;   // the same in the device's view
     int32_t* h_cnt3 = nullptr;     // pinned [2 slots][4]: the adjoint forward's batch counts
     int last_adj_groups = 0, last_adj_group_size = 0, last_adj_segments = 0;
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -113,11 +114,19 @@ template <typename T> struct Impl : ImplBase {
     double* d_stage = nullptr;     // field staging, max over catchments of (ny+1)*(nx+1) doubles
     size_t stage_elems = 0;
 
-    // graph of G (plan, step) pairs
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    // captured batches of G steps (and of kShort, for the end of a call)
+    hipGraph_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int G = 16;
+    static constexpr int kShort = 4;
     bool use_graph = true;
+
+    // second copies for steps that plan themselves (see StepPlan), and that plan's catchments
+    double *t2 = nullptr, *dt_last = nullptr;
+    int64_t* steps2 = nullptr;
+    int32_t *par2 = nullptr, *fault2 = nullptr;
+    HB* hbins4 = nullptr;            // copies 1 to 3 of the depth-maximum bins
+    PlanCatch* d_pc = nullptr;
 
     // kernel timing
     bool timing_on = false;      // per-launch events (graph capture off while on)
@@ -274,8 +283,7 @@ template <typename T> struct Impl : ImplBase {
     ~Impl() override {
         (void)hipStreamSynchronize(st);
         adj_free_all();
-        if (gexec) (void)hipGraphExecDestroy(gexec);
-        if (graph) (void)hipGraphDestroy(graph);
+        invalidate_graph();
         for (auto e : ev)
             if (e) (void)hipEventDestroy(e);
         for (auto e : tev) (void)hipEventDestroy(e);
@@ -385,10 +393,60 @@ template <typename T> struct Impl : ImplBase {
     }
 
     void invalidate_graph() {
-        if (gexec) (void)hipGraphExecDestroy(gexec);
-        if (graph) (void)hipGraphDestroy(graph);
-        gexec = nullptr;
-        graph = nullptr;
+        for (int k = 0; k < 2; ++k) {
+            if (gexec[k]) (void)hipGraphExecDestroy(gexec[k]);
+            if (graph[k]) (void)hipGraphDestroy(graph[k]);
+            gexec[k] = nullptr;
+            graph[k] = nullptr;
+        }
+    }
+
+    // Whether the steps plan themselves: the row march, in batches of whole rounds of
+    // four.  At every size: calls of flood_step over 512 x 512 x 16 8.9 -> 7.6 ms,
+    // 1024 x 1024 x 16 with inflow 26.7 -> 22.7 ms, 1024 x 1024 x 32 91 -> 79 ms, and 2000 x
+    // 2000 x 96, where the planning of 200,000 wavefronts is hidden behind their loads,
+    // 310 -> 308 ms.
+    bool self_planned() const { return variant == 3 && G % 4 == 0; }
+
+    // step i of a batch
+    void launch_one(int i) {
+        if (!self_planned()) {
+            launch_plan<T>(PL, st);
+            launch_steps(SL);
+            return;
+        }
+        StepLaunch<T> L = SL;
+        StepPlan<T>& P = L.plan;
+        HB* bins[4];
+        for (int k = 0; k < 4; ++k) bins[k] = k ? hbins4 + (size_t)(k - 1) * kBins * n_total : hbins;
+        const bool o = i & 1;
+        P.pc = d_pc;
+        P.t_end = d_tend;
+        P.t_in = o ? t2 : t;
+        P.t_out = o ? t : t2;
+        P.steps_in = o ? steps2 : steps;
+        P.steps_out = o ? steps : steps2;
+        P.par_in = o ? par2 : par;
+        P.par_out = o ? par : par2;
+        P.fault_in = o ? fault2 : fault;
+        P.fault_out = o ? fault : fault2;
+        P.bins_in = bins[i & 3];
+        P.bins_out = bins[(i + 1) & 3];
+        P.bins_clear = bins[(i + 2) & 3];
+        P.s = s;
+        P.mu = mu;
+        P.clsn = PL.clsn;
+        P.drain = PL.drain;
+        P.lim = step_lim;
+        P.vrain = vrain;
+        P.vin = vin;
+        P.dt_last = dt_last;
+        P.dtlog = dtlog;
+        P.telog = telog;
+        P.log_n = log_n;
+        P.dtlog_cap = log_cap;
+        P.status = status;
+        launch_steps(L);
     }
 
     flood_status init(int nc, const flood_grid* grids, const flood_params* params, const int32_t* members,
@@ -622,9 +680,16 @@ template <typename T> struct Impl : ImplBase {
         CHK(dalloc(&fault, n_total, err));
         CHK(dalloc(&status, 1, err));
         CHK(dalloc(&hbins, (size_t)kBins * n_total, err));
+        CHK(dalloc(&hbins4, (size_t)3 * kBins * n_total, err));
+        CHK(dalloc(&t2, n_total, err));
+        CHK(dalloc(&dt_last, n_total, err));
+        CHK(dalloc(&steps2, n_total, err));
+        CHK(dalloc(&par2, n_total, err));
+        CHK(dalloc(&fault2, n_total, err));
+        CHK(dalloc(&d_pc, nc, err));
         CHK(dalloc(&ms, n_total, err));
         CHK(dalloc(&d_tend, 1, err));
-        CHK(dalloc(&d_count, 2, err));
+        CHK(dalloc(&d_count, 3, err));
         {
             std::vector<double> hs(n_total), hm(n_total), hl(n_total), z0(n_total, 0.0);
             std::vector<double> hcn((size_t)n_total * kMaxClasses, 0.0), hdr(n_total, 0.0);
@@ -661,6 +726,8 @@ template <typename T> struct Impl : ImplBase {
         HIPCHK(hipMemsetAsync(fault, 0, n_total * sizeof(int32_t), st));
         HIPCHK(hipMemsetAsync(status, 0, sizeof(int32_t), st));
         HIPCHK(hipMemsetAsync(hbins, 0, (size_t)kBins * n_total * sizeof(HB), st));
+        HIPCHK(hipMemsetAsync(hbins4, 0, (size_t)3 * kBins * n_total * sizeof(HB), st));
+        HIPCHK(hipMemsetAsync(dt_last, 0, n_total * sizeof(double), st));
         HIPCHK(hipMemsetAsync(ms, 0, n_total * sizeof(MemberStep<T>), st));
 
         // scratch
@@ -676,8 +743,9 @@ template <typename T> struct Impl : ImplBase {
         CHK(dalloc(&d_flag, 1, err));
         CHK(dalloc(&d_stage, stage_elems, err));
         HIPCHK(hipHostMalloc((void**)&h_tend, sizeof(double), hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void**)&h_count, 4 * sizeof(int32_t), hipHostMallocDefault));
-        std::memset(h_count, 0, 4 * sizeof(int32_t));
+        HIPCHK(hipHostMalloc((void**)&h_count, 8 * sizeof(int32_t), hipHostMallocDefault));
+        std::memset(h_count, 0, 8 * sizeof(int32_t));
+        HIPCHK(hipHostGetDevicePointer((void**)&d_hcount, h_count, 0));
         HIPCHK(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
 
@@ -718,7 +786,9 @@ template <typename T> struct Impl : ImplBase {
             pc.n_series = c.n_series;
             for (int k = 0; k < kMaxSeries; ++k) pc.wq[k] = c.wq[k];
         }
+        HIPCHK(hipMemcpy(d_pc, PL.c, nc * sizeof(PlanCatch), hipMemcpyHostToDevice));
         PL.t_end = d_tend;
+        PL.dt_last = dt_last;
         PL.t = t;
         PL.s = s;
         PL.mu = mu;
@@ -746,6 +816,7 @@ template <typename T> struct Impl : ImplBase {
         PL.tag_value = -1;
         SL.recompute = 0;
         SL.clamp_out = nullptr;
+        SL.plan = StepPlan<T>{};
         layout_launch();
         for (int i = 0; i < nc; ++i) launch_hmax_init<T>(mi, cats[i].dev, par, hbins, n_total, st);
         HIPCHK(hipGetLastError());
@@ -901,6 +972,9 @@ template <typename T> struct Impl : ImplBase {
                 HIPCHK(hipEventElapsedTime(&ms_el, a, b));
                 best_rep = std::min(best_rep, ms_el);
             }
+            // kernels whose steps do not plan themselves need a planner launch before each
+            // (4-5 us for few members, with a launch gap of 4 us), which the trial leaves out
+            if (!self_planned()) best_rep += 8e-3f;
             *out = best_rep;
             return FLOOD_OK;
         };
@@ -1043,31 +1117,27 @@ template <typename T> struct Impl : ImplBase {
     // stepping
     // ---------------------------------------------------------------------
     flood_status ensure_graph(std::string& err) {
-        if (!use_graph || gexec || timing_on) return FLOOD_OK;
-        hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            use_graph = false;
-            return FLOOD_OK;
-        }
-        for (int i = 0; i < G; ++i) {
-            launch_plan<T>(PL, st);
-            launch_steps(SL);
-        }
-        e = hipStreamEndCapture(st, &graph);
-        if (e != hipSuccess || !graph) {
-            (void)hipGetLastError();
-            use_graph = false;
-            graph = nullptr;
-            return FLOOD_OK;
-        }
-        e = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipGraphDestroy(graph);
-            graph = nullptr;
-            gexec = nullptr;
-            use_graph = false;
+        if (!use_graph || gexec[0] || timing_on) return FLOOD_OK;
+        for (int k = 0; k < 2; ++k) {
+            const int n = k ? kShort : G;
+            if (k && (G % kShort || G == kShort)) break;   // batches of G only
+            hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                invalidate_graph();
+                use_graph = false;
+                return FLOOD_OK;
+            }
+            for (int i = 0; i < n; ++i) launch_one(i);
+            e = hipStreamEndCapture(st, &graph[k]);
+            if (e == hipSuccess && graph[k]) e = hipGraphInstantiate(&gexec[k], graph[k], nullptr, nullptr, 0);
+            if (e != hipSuccess || !gexec[k]) {
+                (void)hipGetLastError();
+                gexec[k] = nullptr;
+                invalidate_graph();
+                use_graph = false;
+                return FLOOD_OK;
+            }
         }
         (void)err;
         return FLOOD_OK;
@@ -1084,24 +1154,30 @@ template <typename T> struct Impl : ImplBase {
         return FLOOD_OK;
     }
 
-    flood_status launch_batch(int slot, std::string& err) {
+    // n steps of every member (G, or kShort where there is a graph for it); the counts
+    // after them go straight into the pinned block (no copy command per batch)
+    flood_status launch_batch(int slot, int n, std::string& err) {
         if (timing_batch) {
-            if (next_event_pair(G)) { err = "hipEventCreate failed"; return FLOOD_EHIP; }
+            if (next_event_pair(n)) { err = "hipEventCreate failed"; return FLOOD_EHIP; }
             HIPCHK(hipEventRecord(tev[tev_used], st));
         }
-        if (gexec && !timing_on) {
-            HIPCHK(hipGraphLaunch(gexec, st));
+        hipGraphExec_t ge = timing_on ? nullptr : gexec[n == G ? 0 : 1];
+        if (ge) {
+            HIPCHK(hipGraphLaunch(ge, st));
         } else {
-            for (int i = 0; i < G; ++i) {
-                launch_plan<T>(PL, st);
+            for (int i = 0; i < n; ++i) {
                 if (timing_on) {
                     if (next_event_pair(1)) { err = "hipEventCreate failed"; return FLOOD_EHIP; }
+                    if (!self_planned()) launch_plan<T>(PL, st);
                     HIPCHK(hipEventRecord(tev[tev_used], st));
-                    launch_steps(SL);
+                    if (self_planned())
+                        launch_one(i);
+                    else
+                        launch_steps(SL);
                     HIPCHK(hipEventRecord(tev[tev_used + 1], st));
                     tev_used += 2;
                 } else {
-                    launch_steps(SL);
+                    launch_one(i);
                 }
             }
         }
@@ -1109,9 +1185,8 @@ template <typename T> struct Impl : ImplBase {
             HIPCHK(hipEventRecord(tev[tev_used + 1], st));
             tev_used += 2;
         }
-        launch_count_active(n_total, t, fault, d_tend, status, steps, step_lim, d_count, st);
+        launch_count_active(n_total, t, fault, d_tend, status, steps, step_lim, dt_last, d_hcount + 4 * slot, st);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(h_count + 2 * slot, d_count, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
         HIPCHK(hipEventRecord(ev[slot], st));
         return FLOOD_OK;
     }
@@ -1119,30 +1194,43 @@ template <typename T> struct Impl : ImplBase {
     flood_status step(double t_end, int64_t max_steps, std::string& err) override {
         CHK(ensure_graph(err));
         // a status word is only read for batches launched by this call
-        std::memset(h_count, 0, 4 * sizeof(int32_t));
+        std::memset(h_count, 0, 8 * sizeof(int32_t));
         *h_tend = t_end;
         HIPCHK(hipMemcpyAsync(d_tend, h_tend, sizeof(double), hipMemcpyHostToDevice, st));
         launch_step_limit(n_total, steps, max_steps, step_lim, st);
-        // the first batch runs alone (a call that needs a single batch launches nothing
-        // more); after that two batches are kept in flight
-        CHK(launch_batch(0, err));
-        HIPCHK(hipEventSynchronize(ev[0]));
-        int slot = 0;
-        if (h_count[0] != 0) {
-            CHK(launch_batch(1, err));
-            CHK(launch_batch(0, err));
-            slot = 1;
-            int64_t batches = 3;
-            const int64_t max_batches = (int64_t)50000000 / G;
-            for (;;) {
-                HIPCHK(hipEventSynchronize(ev[slot]));
-                if (h_count[2 * slot] == 0) break;
-                if (batches > max_batches) {
-                    err = "step limit exceeded before every member reached t_end";
-                    return FLOOD_ESTATE;
-                }
-                CHK(launch_batch(slot, err));
-                ++batches;
+        // Up to two batches are in flight, so that the device does not wait for the host.
+        // The first runs alone (a call that needs one batch launches no more); after it
+        // the steps still needed are estimated from the step lengths, and what is
+        // launched beyond them is kept to a short batch.  (Two full batches past the end
+        // were 20 of 224 launches of a 600-s call on 128 x 128 cells.)
+        const int small = (gexec[1] || (!gexec[0] && self_planned() && G > kShort)) ? kShort : G;
+        int64_t launched = 0;
+        const int64_t most = (int64_t)50000000;
+        int64_t pending[2] = {0, 0};      // steps of the batch in each slot, 0: none in flight
+        int slot = 0;                     // the slot to wait for next
+        auto put = [&](int sl, int n) -> flood_status {
+            CHK(launch_batch(sl, n, err));
+            pending[sl] = n;
+            launched += n;
+            return FLOOD_OK;
+        };
+        CHK(put(0, max_steps > 0 && max_steps <= small ? small : G));
+        for (;;) {
+            HIPCHK(hipEventSynchronize(ev[slot]));
+            pending[slot] = 0;
+            if (h_count[4 * slot] == 0) break;
+            if (launched > most) {
+                err = "step limit exceeded before every member reached t_end";
+                return FLOOD_ESTATE;
+            }
+            // steps needed after the batch just finished, less those already on their way
+            int64_t need = (int64_t)h_count[4 * slot + 2] - pending[slot ^ 1];
+            if (pending[slot ^ 1] == 0) {
+                CHK(put(slot, need > small ? G : small));
+                need -= pending[slot];
+                if (need > 0) CHK(put(slot ^ 1, need > small ? G : small));
+            } else {
+                if (need > 0) CHK(put(slot, need > small ? G : small));
                 slot ^= 1;
             }
         }
@@ -1156,8 +1244,8 @@ template <typename T> struct Impl : ImplBase {
             }
             tev_used = 0;
         }
-        // status words of the batches this call launched (slot 1 only when more than one batch ran)
-        const int stat = h_count[2 * (slot ^ 1) + 1] | h_count[2 * slot + 1];
+        // status words of the batches this call launched
+        const int stat = h_count[1] | h_count[4 + 1];
         if (stat) {
             err = "a member's depth became non-finite or too large to advance its clock; it was frozen";
             return FLOOD_ENUMERIC;
@@ -1733,7 +1821,7 @@ template <typename T> struct Impl : ImplBase {
         if (omi) *omi = mi;
         if (rows) *rows = cats[0].tile_rows;
         if (cpb) *cpb = std::min(cats[0].cpb, cats[0].n_chunks);
-        if (gs) *gs = (use_graph && gexec) ? G : 0;
+        if (gs) *gs = (use_graph && gexec[0]) ? G : 0;
         if (vk) *vk = variant;
         if (mr) *mr = std::min(cats[0].march_rows, cats[0].ny);
     }
@@ -2505,7 +2593,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
                     launch_step_mi<T>(mi, SLg, st);
                     ++L;
                 }
-                launch_count_active(Gg, t + off + g0, fault + off + g0, d_tend, status, nullptr, nullptr, d_count, st);
+                launch_count_active(Gg, t + off + g0, fault + off + g0, d_tend, status, nullptr, nullptr, nullptr, d_count, st);
                 HIPCHK(hipGetLastError());
                 HIPCHK(hipMemcpyAsync(h_count, d_count, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
                 HIPCHK(hipStreamSynchronize(st));

@@ -78,3 +78,40 @@ def test_stores_under_load(fl):
     for m in range(4):
         for w in (fl.FIELD_H, fl.FIELD_QX, fl.FIELD_QY):
             np.testing.assert_array_equal(ens[0].field(m, w), ens[1].field(m, w))
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+def test_steps_that_plan_themselves(fl, monkeypatch, rb):
+    # batches of three steps are planned by the planner kernel, batches of four or sixteen by
+    # the steps: the same clocks, logs, ledgers and states, with bounded calls, calls that move
+    # nothing, rain-block edges, a member that faults and catchments of different sizes
+    cats = [_catch(40, 128, 3, seed=5), _catch(21, 64, 2, (0, 1, 0, 1), seed=6)]
+
+    def run(batch):
+        monkeypatch.setenv("FLOOD_GRAPH_STEPS", str(batch))
+        e = fl.FloodEnsemble(cats, RAIN, rain_interval=7.0, real_bytes=rb, step_kernel=3, march_rows=8)
+        e.log_steps(256)
+        e.step_n(30.0, 5)
+        e.step(3.0)
+        e.step(9.5)
+        h = e.field(1)
+        h[3, 3] = 3e38 if rb == 4 else 1e300        # Eq. 4 no longer advances this member's clock
+        e.set_state(1, h, e.field(1, fl.FIELD_QX), e.field(1, fl.FIELD_QY), 9.5)
+        try:
+            e.step(25.0)
+            status = 0
+        except fl.FloodError as err:
+            status = err.status
+        out = [status]
+        for c in range(2):
+            led = e.ledger(c)
+            out += [led[k] for k in ("rain_in", "t", "steps", "inflow", "drain")] + list(e.step_log(c))
+            out += [e.field(m, w, c) for m in range(cats[c]["n_members"]) for w in (0, 1, 2)]
+        return out
+
+    ref = run(3)
+    assert ref[0] == fl.FLOOD_ENUMERIC
+    for batch in (4, 16):
+        got = run(batch)
+        for a, b in zip(ref, got):
+            np.testing.assert_array_equal(a, b)
