@@ -52,7 +52,21 @@ __device__ __forceinline__ float pow_m73(float h) {
     const float y = y0 + y0 * ((1.0f - t) * 0.333333343f);
     return y * __builtin_amdgcn_rcpf(h * h);
 }
-__device__ __forceinline__ double pow_m73(double h) { return 1.0 / pow(h, 7.0 / 3.0); }
+// Double precision: h = m 2^(3k), m in [1/2, 8); m^(-1/3) starts from the single
+// precision y0 above (error 1e-7) and takes two terms of (1 - r)^(-1/3) = 1 + r / 3 +
+// 2 r^2 / 9 + ..., r = 1 - m y0^3 (the third is 1e-20); y0^2 is exact and r is formed
+// with one rounding.  About 35 instructions where pow and a division take some 250:
+// an FP64 step is bound by them, and on small grids by fetching them.  Error over h in
+// [1e-6, 1e3]: 2.3 ulp at most, 0.43 on average (1 / pow(h, 7.0 / 3.0): 20 and 5.6,
+// from the rounding of the exponent).
+__device__ __forceinline__ double pow_m73(double h) {
+    const int k = (__builtin_amdgcn_frexp_exp(h) * 21845) >> 16;
+    const double m = ldexp(h, -3 * k);
+    const double y0 = (double)__builtin_amdgcn_exp2f(-0.333333343f * __builtin_amdgcn_logf((float)m));
+    const double r = __builtin_fma(-(m * y0), y0 * y0, 1.0);
+    const double y = __builtin_fma(y0, r * __builtin_fma(r, 2.0 / 9.0, 1.0 / 3.0), y0);
+    return ldexp(y, -k) / (h * h);
+}
 
 __device__ __forceinline__ float qdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 __device__ __forceinline__ double qdiv(double a, double b) { return a / b; }
