@@ -19,40 +19,51 @@ namespace flood {
 // to the old discharge q, the two depths, and (cn) the Manning value of either
 // adjacent cell: A = G s^2 dt hf^(-7/3) with G = g nf^2 and nf = (n1 + n2)/2,
 // so dF/dn_i = -F|q|/D * g nf s^2 dt hf^(-7/3).  Gn = g nf.
+// c1, c2: the cells' limiter products h capf; A0 = G s^2 dt.
 template <typename T>
-__device__ __forceinline__ void link_in_d(T q, T h1, T h2, T dz, T G, T Gn, const MemberStep<T>& ms, T hdry,
-                                          T& dq, T& dh1, T& dh2, T& cn) {
+__device__ __forceinline__ void link_core_d(T q, T h1, T h2, T c1, T c2, T dz, T A0, T Gn, const MemberStep<T>& ms, T hdry,
+                                            T& dq, T& dh1, T& dh2, T& cn) {
     // evaluated without branches and selected at the end, as in the forward:
     // dry, limited and free links in one wavefront do not split it, and a dry
     // link's intermediate values (possibly inf or NaN) are discarded
     const T d = h1 - h2;
     const bool up1 = d >= dz;
-    const T hf = link_depth(h1, h2, dz);
+    const T hf = (up1 ? h1 : h2) - fmax(up1 ? dz : -dz, T(0));   // link_depth
     const bool wet = hf > hdry;
     const T p = pow_m73(hf);
-    const T A = G * ms.s2dt * p;
+    const T A = A0 * p;
     const T aq = fabs(q);
     const T D = T(1) + A * aq;
-    const T num = q - ms.gdtdx * hf * (dz - d);
+    const T slope = dz - d;                          // dx times the surface slope
+    const T num = q - ms.gdtdx * hf * slope;
     const T invD = qdiv(T(1), D);
     const T F = qdiv(num, D);
-    const T sg = q > T(0) ? T(1) : (q < T(0) ? T(-1) : T(0));
     // donor limiter: a limited link depends on its upwind depth only
     const bool pos = F > T(0);
-    const bool cap1 = pos && (h1 * ms.capf < F);
-    const bool cap2 = !pos && (F < -h2 * ms.capf);
-    const bool free_ = wet && !cap1 && !cap2;
-    const T slope = dz - d;                          // dx times the surface slope
+    const bool cap1 = pos & (c1 < F);
+    const bool cap2 = !pos & (F < -c2);
+    const bool free_ = wet & !cap1 & !cap2;
     const T dDdhf = T(-7.0 / 3.0) * A * aq * qdiv(T(1), hf);
     const T t_hf = -ms.gdtdx * slope - F * dDdhf;    // d(num - F D)/d(hf)
-    const T dq_ = (T(1) - F * A * sg) * invD;
-    const T dh1_ = ((up1 ? t_hf : T(0)) + ms.gdtdx * hf) * invD;
-    const T dh2_ = ((up1 ? T(0) : t_hf) - ms.gdtdx * hf) * invD;
+    const T FA = F * A;                              // times sign(q), with sign(0) = 0
+    const T dq_ = (T(1) - (q > T(0) ? FA : (q < T(0) ? -FA : T(0)))) * invD;
+    const T gh = ms.gdtdx * hf;
+    const T dh1_ = ((up1 ? t_hf : T(0)) + gh) * invD;
+    const T dh2_ = ((up1 ? T(0) : t_hf) - gh) * invD;
     const T cn_ = -F * aq * invD * Gn * ms.s2dt * p;
-    dq = free_ ? dq_ : T(0);
-    cn = free_ ? cn_ : T(0);
-    dh1 = !wet ? T(0) : (cap1 ? ms.capf : (cap2 ? T(0) : dh1_));
-    dh2 = !wet ? T(0) : (cap2 ? -ms.capf : (cap1 ? T(0) : dh2_));
+    // (without the hint the compiler makes branches of these selects and moves the
+    // arithmetic above behind them, link by link)
+    const bool keep = __builtin_unpredictable(free_);
+    dq = keep ? dq_ : T(0);
+    cn = keep ? cn_ : T(0);
+    dh1 = keep ? dh1_ : (__builtin_unpredictable(wet & cap1) ? ms.capf : T(0));
+    dh2 = keep ? dh2_ : (__builtin_unpredictable(wet & cap2) ? -ms.capf : T(0));
+}
+
+template <typename T>
+__device__ __forceinline__ void link_in_d(T q, T h1, T h2, T dz, T G, T Gn, const MemberStep<T>& ms, T hdry,
+                                          T& dq, T& dh1, T& dh2, T& cn) {
+    link_core_d(q, h1, h2, h1 * ms.capf, h2 * ms.capf, dz, G * ms.s2dt, Gn, ms, hdry, dq, dh1, dh2, cn);
 }
 
 // Open edge link (outward discharge qo, inner depth h), partials with respect
@@ -309,9 +320,26 @@ template <typename T> void launch_adjoint_step(int mi, const AdjLaunch<T>& A, hi
 // of that step reads the adjoint of its new depths already masked.  The
 // rain-multiplier adjoint is accumulated per (strip, member).  Members that do
 // not step in this launch (or pad the last quad) skip the march and keep their
-// adjoint in place, but still meet the workgroup barrier.  PF = 1 issues the
-// next row's loads before the current row's derivatives (one row of lookahead).
-template <typename T, int V, int PF>
+// adjoint in place, but still meet the workgroup barrier.
+//
+// Bound by vector issue and HBM alike, so it is built as the forward march is: row
+// streams behind buffer descriptors (lanes outside the grid switched off by the
+// range check), the next row's loads issued before the current row's
+// derivatives, two rows per iteration so that the register sets of the two swap
+// roles, DPP lane shifts, limiter products shared by a cell's links, and the
+// domain's north and west edge links taken before the row loop (the west ones a
+// row per lane), so that the loop holds no memory access but its streams.
+// Measured, against a march that fetched edge links and neighbours inside the row
+// loop: 64 x 96 x 4 in FP64 22 us a step from 27 (8-row strips), 1024 x 1024 x 16 in
+// FP32 128 us from 130 (742 MB of traffic, 646 MB of it unavoidable, 4.7 TB/s with all
+// members stepping); five waves per SIMD instead of four spilled and cost 4 %.
+template <typename T, int V>
+struct AdjRow {
+    T qE[V], qS[V], lqE[V], lqS[V];    // a row's links and their adjoints
+    T hs[V], zs[V], ns[V], les[V];     // the row below it
+};
+
+template <typename T, int V>
 __global__ __launch_bounds__(kBlock) void k_adjv(const AdjvLaunch<T> A) {
     extern __shared__ unsigned char adj_lds[];
     const CatchDev<T>& C = A.c;
@@ -335,7 +363,7 @@ __global__ __launch_bounds__(kBlock) void k_adjv(const AdjvLaunch<T> A) {
     const bool own = lane >= 1 && lane <= 62 && inx;
     const bool westw = sx == 0;                        // wavefront-uniform edge tests
     const bool eastw = sx == C.strips_xa - 1;
-    const int xa = min(max(xl, 0), nx - V);            // load column (lanes outside the grid read, never use)
+    const int xa = min(max(xl, 0), nx - V);
     const int r0 = sy * C.march_rows;
     const int r1 = min(r0 + C.march_rows, ny);
     const size_t plane = (size_t)ny * nx;
@@ -347,220 +375,233 @@ __global__ __launch_bounds__(kBlock) void k_adjv(const AdjvLaunch<T> A) {
         const MemberStep<T> ms = A.rec[rr];
         const double rdt = A.rec_rdt[rr];
         const int tag_prev = (jst >= 1 && A.n_gauges > 0) ? A.rec_tag[rr - A.stride] : -1;
-        const size_t bs = (size_t)ms.blk;
-        const T* __restrict__ H = C.h[0] + bs * plane;
-        const T* __restrict__ QX = C.qx[0] + bs * plane;
-        const T* __restrict__ QY = C.qy[0] + bs * plane;
-        const T* __restrict__ QWs = C.qw[0] + bs * ny;
-        const T* __restrict__ QNs = C.qn[0] + bs * nx;
-        const int lp = A.lbase[k] ^ (A.i & 1);
-        const T* __restrict__ LH = A.lh[lp] + (size_t)k * plane;
-        const T* __restrict__ LQX = A.lqx[lp] + (size_t)k * plane;
-        const T* __restrict__ LQY = A.lqy[lp] + (size_t)k * plane;
-        const T* __restrict__ LQWs = A.lqw[lp] + (size_t)k * ny;
-        const T* __restrict__ LQNs = A.lqn[lp] + (size_t)k * nx;
-        T* __restrict__ LHo = A.lh[lp ^ 1] + (size_t)k * plane;
-        T* __restrict__ LQXo = A.lqx[lp ^ 1] + (size_t)k * plane;
-        T* __restrict__ LQYo = A.lqy[lp ^ 1] + (size_t)k * plane;
-        T* __restrict__ LQWo = A.lqw[lp ^ 1] + (size_t)k * ny;
-        T* __restrict__ LQNo = A.lqn[lp ^ 1] + (size_t)k * nx;
-        const T* __restrict__ Z = C.z;
-        const T* __restrict__ Nn = C.n;
+        const size_t bs = (size_t)__builtin_amdgcn_readfirstlane(ms.blk);
+        const bool l1 = __builtin_amdgcn_readfirstlane(A.lbase[k] ^ (A.i & 1)) != 0;
+        const uint32_t es = (uint32_t)sizeof(T);
+        const uint32_t pitch = (uint32_t)nx * es, bytes = (uint32_t)plane * es;
+        Rows<T> H, QX, QY, LH, LQX, LQY, LHo, LQXo, LQYo, Z, NM;
+        H.set(C.h[0] + bs * plane, bytes);
+        QX.set(C.qx[0] + bs * plane, bytes);
+        QY.set(C.qy[0] + bs * plane, bytes);
+        const size_t mk = (size_t)k * plane;
+        LH.set((l1 ? A.lh[1] : A.lh[0]) + mk, bytes);
+        LQX.set((l1 ? A.lqx[1] : A.lqx[0]) + mk, bytes);
+        LQY.set((l1 ? A.lqy[1] : A.lqy[0]) + mk, bytes);
+        LHo.set((l1 ? A.lh[0] : A.lh[1]) + mk, bytes);
+        LQXo.set((l1 ? A.lqx[0] : A.lqx[1]) + mk, bytes);
+        LQYo.set((l1 ? A.lqy[0] : A.lqy[1]) + mk, bytes);
+        const T* QWs = C.qw[0] + bs * ny;
+        const T* QNs = C.qn[0] + bs * nx;
+        const T* LQWs = (l1 ? A.lqw[1] : A.lqw[0]) + (size_t)k * ny;
+        const T* LQNs = (l1 ? A.lqn[1] : A.lqn[0]) + (size_t)k * nx;
+        T* LQWo = (l1 ? A.lqw[0] : A.lqw[1]) + (size_t)k * ny;
+        T* LQNo = (l1 ? A.lqn[0] : A.lqn[1]) + (size_t)k * nx;
+        Z.set(C.z, bytes);
+        NM.set(C.n, bytes);
         const T g = C.g, hdry = C.hdry, kk = ms.dtdx;
+        // Manning factors of a link from the sum of its cells' values: g nf^2 s^2 dt and
+        // g nf, nf the mean (the halvings, exact, are in g4 and g2)
+        const T g4 = T(0.25) * g, g2 = T(0.5) * g;
 
-        size_t ca = (size_t)r0 * nx + xa;
-        T hc[V], zc[V], nc[V], lec[V], pNh[V], pNn[V];
-        vload<T, V>(H + ca, hc);
-        vload<T, V>(Z + ca, zc);
-        vload<T, V>(Nn + ca, nc);
-        vload<T, V>(LH + ca, lec);
-        if (r0 > 0) {
-            // the south links of the row above the strip feed its first row's north links
+        const uint32_t xo = inx ? (uint32_t)xl * es : kPastEnd;
+        uint32_t so = (uint32_t)r0 * pitch;
+        uint32_t vo = own ? xo + so : kPastEnd;
+        const uint32_t vp = own ? pitch : 0u;
+        auto load_row = [&](uint32_t at, bool below, AdjRow<T, V>& m) {
+            const uint32_t sb = below ? at + pitch : at;
+            QX.template load<V, false>(xo, at, m.qE);
+            QY.template load<V, false>(xo, at, m.qS);
+            LQX.template load<V, false>(xo, at, m.lqE);
+            LQY.template load<V, false>(xo, at, m.lqS);
+            H.template load<V, false>(xo, sb, m.hs);
+            Z.template load<V, false>(xo, sb, m.zs);
+            NM.template load<V, false>(xo, sb, m.ns);
+            LH.template load<V, false>(xo, sb, m.les);
+        };
+        T hc[V], zc[V], nc[V], lec[V], cc[V], pNh[V], pNn[V];
+        AdjRow<T, V> a, b;
+        // west edge links of the domain, lane i that of row r0 + i (strips are at most 16
+        // rows tall): what they add to the depth and roughness adjoints of their inner cell
+        T bNh = T(0), bNn = T(0);
+        {
             T hN[V], zN[V], nN[V], qN[V], lqN[V], leN[V];
-            vload<T, V>(H + ca - nx, hN);
-            vload<T, V>(Z + ca - nx, zN);
-            vload<T, V>(Nn + ca - nx, nN);
-            vload<T, V>(QY + ca - nx, qN);
-            vload<T, V>(LQY + ca - nx, lqN);
-            vload<T, V>(LH + ca - nx, leN);
-    #pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const T nf = T(0.5) * (nN[j] + nc[j]);
-                T dq, d1, d2, cn;
-                link_in_d(qN[j], hN[j], hc[j], zc[j] - zN[j], g * (nf * nf), g * nf, ms, hdry, dq, d1, d2, cn);
-                const T lt = lqN[j] + kk * (lec[j] - leN[j]);
-                pNh[j] = lt * d2;
-                pNn[j] = lt * cn;
+            H.template load<V, false>(xo, so, hc);
+            Z.template load<V, false>(xo, so, zc);
+            NM.template load<V, false>(xo, so, nc);
+            LH.template load<V, false>(xo, so, lec);
+            if (r0 > 0) {
+                // the south links of the row above the strip feed its first row's north links
+                const uint32_t sn = so - pitch;
+                H.template load<V, false>(xo, sn, hN);
+                Z.template load<V, false>(xo, sn, zN);
+                NM.template load<V, false>(xo, sn, nN);
+                QY.template load<V, false>(xo, sn, qN);
+                LQY.template load<V, false>(xo, sn, lqN);
+                LH.template load<V, false>(xo, sn, leN);
             }
-        } else {
-    #pragma unroll
-            for (int j = 0; j < V; ++j) pNh[j] = pNn[j] = T(0);
+            load_row(so, r0 + 1 < ny, a);
+            if (westw) {
+                const int rw = min(r0 + lane, r1 - 1);
+                T oqw = T(0);
+                if (C.edge_open[3]) {
+                    const uint32_t cw = (uint32_t)rw * pitch;
+                    const T h0 = H.load1(cw, 0), n0 = NM.load1(cw, 0), l0 = LH.load1(cw, 0);
+                    T dq, d1, cn;
+                    link_open_d(-QWs[rw], h0, g * (n0 * n0), T(2) * g * n0, C.edge_slope[3], ms, hdry, dq, d1, cn);
+                    const T lt = LQWs[rw] + kk * l0;
+                    oqw = lt * dq;
+                    bNh = -(lt * d1);
+                    bNn = -(lt * cn);
+                }
+                if (r0 + lane < r1) LQWo[rw] = oqw;   // the strip holds -qo
+            }
+#pragma unroll
+            for (int j = 0; j < V; ++j) cc[j] = hc[j] * ms.capf;
+            if (r0 > 0) {
+#pragma unroll
+                for (int j = 0; j < V; ++j) {
+                    const T n = nN[j] + nc[j];
+                    T dq, d1, d2, cn;
+                    link_core_d(qN[j], hN[j], hc[j], hN[j] * ms.capf, cc[j], zc[j] - zN[j], g4 * (n * n) * ms.s2dt, g2 * n,
+                                ms, hdry, dq, d1, d2, cn);
+                    const T lt = lqN[j] + kk * (lec[j] - leN[j]);
+                    pNh[j] = lt * d2;
+                    pNn[j] = lt * cn;
+                }
+            } else {
+                // north edge links of the domain; their strip holds -qo
+#pragma unroll
+                for (int j = 0; j < V; ++j) {
+                    T oqn = T(0);
+                    pNh[j] = pNn[j] = T(0);
+                    if (C.edge_open[0] && inx) {
+                        T dq, d1, cn;
+                        link_open_d(-QNs[xl + j], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[0], ms, hdry,
+                                    dq, d1, cn);
+                        const T lt = LQNs[xl + j] + kk * lec[j];
+                        oqn = lt * dq;
+                        pNh[j] = -(lt * d1);
+                        pNn[j] = -(lt * cn);
+                    }
+                    if (own) LQNo[xl + j] = oqn;
+                }
+            }
         }
         double lsum = 0.0;
-        // a row's links (qE, qS and their adjoints) and the row below it (hs, zs, ns, les)
-        auto load_row = [&](size_t c, bool below, T (&qe)[V], T (&qs)[V], T (&lqe)[V], T (&lqs)[V], T (&h2)[V],
-                            T (&z2)[V], T (&n2)[V], T (&le2)[V]) {
-            const size_t cb = below ? c + nx : c;
-            vload<T, V>(QX + c, qe);
-            vload<T, V>(QY + c, qs);
-            vload<T, V>(H + cb, h2);
-            vload<T, V>(LQX + c, lqe);
-            vload<T, V>(LQY + c, lqs);
-            vload<T, V>(Z + cb, z2);
-            vload<T, V>(Nn + cb, n2);
-            vload<T, V>(LH + cb, le2);
-        };
-        T qE[V], qS[V], lqE[V], lqS[V], hs[V], zs[V], ns[V], les[V];
-        if (PF) load_row(ca, r0 + 1 < ny, qE, qS, lqE, lqS, hs, zs, ns, les);
-        for (int r = r0; r < r1; ++r) {
-            const bool hasS = r + 1 < ny;
-            T qE2[V], qS2[V], lqE2[V], lqS2[V], hs2[V], zs2[V], ns2[V], les2[V];
-            if (PF) {
-                if (r + 1 < r1) load_row(ca + nx, r + 2 < ny, qE2, qS2, lqE2, lqS2, hs2, zs2, ns2, les2);
-            } else {
-                load_row(ca, hasS, qE, qS, lqE, lqS, hs, zs, ns, les);
-            }
+        auto row = [&](int r, AdjRow<T, V>& m, AdjRow<T, V>& nxt) {
+            load_row(r + 1 < r1 ? so + pitch : so, r + 2 < ny, nxt);
             // east neighbour of the lane's last cell = first cell of the next lane
-            const T hE = __shfl_down(hc[0], 1, 64);
-            const T zE = __shfl_down(zc[0], 1, 64);
-            const T nE = __shfl_down(nc[0], 1, 64);
-            const T leE = __shfl_down(lec[0], 1, 64);
-            T ltE[V], dqE[V], d1E[V], d2E[V], cnE[V];
-    #pragma unroll
+            const T hE = lane_next(hc[0]), zE = lane_next(zc[0]), nE = lane_next(nc[0]), leE = lane_next(lec[0]),
+                    cE = lane_next(cc[0]);
+            T ltE[V], dqE[V], d1E[V], d2E[V], cnE[V], cs[V];
+#pragma unroll
             for (int j = 0; j < V; ++j) {
                 const T h2 = (j + 1 < V) ? hc[j + 1] : hE;
+                const T c2 = (j + 1 < V) ? cc[j + 1] : cE;
                 const T z2 = (j + 1 < V) ? zc[j + 1] : zE;
-                const T n2 = (j + 1 < V) ? nc[j + 1] : nE;
+                const T n = nc[j] + ((j + 1 < V) ? nc[j + 1] : nE);
                 const T le2 = (j + 1 < V) ? lec[j + 1] : leE;
-                const T nf = T(0.5) * (nc[j] + n2);
-                link_in_d(qE[j], hc[j], h2, z2 - zc[j], g * (nf * nf), g * nf, ms, hdry, dqE[j], d1E[j], d2E[j], cnE[j]);
-                ltE[j] = lqE[j] + kk * (le2 - lec[j]);
+                link_core_d(m.qE[j], hc[j], h2, cc[j], c2, z2 - zc[j], g4 * (n * n) * ms.s2dt, g2 * n, ms, hdry, dqE[j],
+                            d1E[j], d2E[j], cnE[j]);
+                ltE[j] = m.lqE[j] + kk * (le2 - lec[j]);
             }
             if (eastw) {
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < V; ++j) {
                     if (xl + j + 1 != nx) continue;
                     d2E[j] = T(0);
                     if (C.edge_open[1]) {
-                        link_open_d(qE[j], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[1], ms, hdry,
+                        link_open_d(m.qE[j], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[1], ms, hdry,
                                     dqE[j], d1E[j], cnE[j]);
-                        ltE[j] = lqE[j] - kk * lec[j];
+                        ltE[j] = m.lqE[j] - kk * lec[j];
                     } else {
                         dqE[j] = d1E[j] = cnE[j] = ltE[j] = T(0);
                     }
                 }
             }
-            // west link of the first cell: the previous lane's last east link
-            const T wH = __shfl_up(ltE[V - 1] * d2E[V - 1], 1, 64);
-            const T wN = __shfl_up(ltE[V - 1] * cnE[V - 1], 1, 64);
+            // what the west links give: the previous lane's last east link, or the domain's edge
+            T wH[V], wN[V];
+            wH[0] = lane_prev(ltE[V - 1] * d2E[V - 1]);
+            wN[0] = lane_prev(ltE[V - 1] * cnE[V - 1]);
+#pragma unroll
+            for (int j = 1; j < V; ++j) {
+                wH[j] = ltE[j - 1] * d2E[j - 1];
+                wN[j] = ltE[j - 1] * cnE[j - 1];
+            }
+            if (westw) {
+                const T eh = lane_pick(bNh, r - r0), en = lane_pick(bNn, r - r0);
+                wH[0] = xl == 0 ? eh : wH[0];
+                wN[0] = xl == 0 ? en : wN[0];
+            }
             // south links
             T ltS[V], dqS[V], d1S[V], d2S[V], cnS[V];
-            if (hasS) {
-    #pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    const T nf = T(0.5) * (nc[j] + ns[j]);
-                    link_in_d(qS[j], hc[j], hs[j], zs[j] - zc[j], g * (nf * nf), g * nf, ms, hdry, dqS[j], d1S[j],
-                              d2S[j], cnS[j]);
-                    ltS[j] = lqS[j] + kk * (les[j] - lec[j]);
-                }
-            } else {
-    #pragma unroll
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                cs[j] = m.hs[j] * ms.capf;
+                const T n = nc[j] + m.ns[j];
+                link_core_d(m.qS[j], hc[j], m.hs[j], cc[j], cs[j], m.zs[j] - zc[j], g4 * (n * n) * ms.s2dt, g2 * n, ms, hdry,
+                            dqS[j], d1S[j], d2S[j], cnS[j]);
+                ltS[j] = m.lqS[j] + kk * (m.les[j] - lec[j]);
+            }
+            if (r + 1 == ny) {
+#pragma unroll
                 for (int j = 0; j < V; ++j) {
                     d2S[j] = T(0);
                     if (C.edge_open[2]) {
-                        link_open_d(qS[j], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[2], ms, hdry,
+                        link_open_d(m.qS[j], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[2], ms, hdry,
                                     dqS[j], d1S[j], cnS[j]);
-                        ltS[j] = lqS[j] - kk * lec[j];
+                        ltS[j] = m.lqS[j] - kk * lec[j];
                     } else {
                         dqS[j] = d1S[j] = cnS[j] = ltS[j] = T(0);
                     }
                 }
             }
-            if (own) {
-                T nh4[V], oqx4[V], oqy4[V], na4[V];
-    #pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    const int x = xl + j;
-                    const T le_c = lec[j];
-                    // east, south (this cell is cell 1), west, north (cell 2), as in k_adj
-                    T nh = le_c;
-                    T nac = T(0);
-                    nh += ltE[j] * d1E[j];
-                    nac += ltE[j] * cnE[j];
-                    nh += ltS[j] * d1S[j];
-                    nac += ltS[j] * cnS[j];
-                    if (j == 0 && westw && x == 0) {
-                        // west edge link; its strip holds -qo
-                        T oqw = T(0);
-                        if (C.edge_open[3]) {
-                            T dq, d1, cn;
-                            link_open_d(-QWs[r], hc[0], g * (nc[0] * nc[0]), T(2) * g * nc[0], C.edge_slope[3], ms,
-                                        hdry, dq, d1, cn);
-                            const T lt = LQWs[r] + kk * le_c;
-                            oqw = lt * dq;
-                            nh -= lt * d1;
-                            nac -= lt * cn;
-                        }
-                        LQWo[r] = oqw;
-                    } else {
-                        nh += (j > 0) ? ltE[j - 1] * d2E[j - 1] : wH;
-                        nac += (j > 0) ? ltE[j - 1] * cnE[j - 1] : wN;
-                    }
-                    if (r > 0) {
-                        nh += pNh[j];
-                        nac += pNn[j];
-                    } else {
-                        // north edge link; its strip holds -qo
-                        T oqn = T(0);
-                        if (C.edge_open[0]) {
-                            T dq, d1, cn;
-                            link_open_d(-QNs[x], hc[j], g * (nc[j] * nc[j]), T(2) * g * nc[j], C.edge_slope[0], ms,
-                                        hdry, dq, d1, cn);
-                            const T lt = LQNs[x] + kk * le_c;
-                            oqn = lt * dq;
-                            nh -= lt * d1;
-                            nac -= lt * cn;
-                        }
-                        LQNo[x] = oqn;
-                    }
-                    // zero where the step before this one clamped the depth (the tape's
-                    // -0): that step's reverse then sees no adjoint of the clamped depth
-                    nh4[j] = clamp_mark(hc[j]) ? T(0) : nh;
-                    oqx4[j] = ltE[j] * dqE[j];
-                    oqy4[j] = ltS[j] * dqS[j];
-                    na4[j] = nac;
-                    lsum += (double)le_c;
-                }
-                vstore<T, V>(LHo + ca, nh4);
-                vstore<T, V>(LQXo + ca, oqx4);
-                vstore<T, V>(LQYo + ca, oqy4);
-    #pragma unroll
-                for (int j = 0; j < V; ++j) NL[((size_t)(r - r0) * 64 + lane) * V + j] = na4[j];
-            }
-    #pragma unroll
+            T nh4[V], oqx4[V], oqy4[V], na4[V];
+#pragma unroll
             for (int j = 0; j < V; ++j) {
-                hc[j] = hs[j];
-                zc[j] = zs[j];
-                nc[j] = ns[j];
-                lec[j] = les[j];
+                // east, south (this cell is cell 1), west, north (cell 2), as in k_adj
+                T nh = lec[j];
+                nh += ltE[j] * d1E[j];
+                nh += ltS[j] * d1S[j];
+                nh += wH[j];
+                nh += pNh[j];
+                T nac = T(0);
+                nac += ltE[j] * cnE[j];
+                nac += ltS[j] * cnS[j];
+                nac += wN[j];
+                nac += pNn[j];
+                // zero where the step before this one clamped the depth (the tape's
+                // -0): that step's reverse then sees no adjoint of the clamped depth
+                nh4[j] = clamp_mark(hc[j]) ? T(0) : nh;
+                oqx4[j] = ltE[j] * dqE[j];
+                oqy4[j] = ltS[j] * dqS[j];
+                na4[j] = nac;
+                lsum += (double)lec[j];
+            }
+            LHo.template store<V, false>(vo, nh4);
+            LQXo.template store<V, false>(vo, oqx4);
+            LQYo.template store<V, false>(vo, oqy4);
+#pragma unroll
+            for (int j = 0; j < V; ++j) NL[((size_t)(r - r0) * 64 + lane) * V + j] = na4[j];
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                hc[j] = m.hs[j];
+                zc[j] = m.zs[j];
+                nc[j] = m.ns[j];
+                lec[j] = m.les[j];
+                cc[j] = cs[j];
                 pNh[j] = ltS[j] * d2S[j];
                 pNn[j] = ltS[j] * cnS[j];
             }
-            if (PF) {
-    #pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    qE[j] = qE2[j];
-                    qS[j] = qS2[j];
-                    lqE[j] = lqE2[j];
-                    lqS[j] = lqS2[j];
-                    hs[j] = hs2[j];
-                    zs[j] = zs2[j];
-                    ns[j] = ns2[j];
-                    les[j] = les2[j];
-                }
-            }
-            ca += nx;
+            so += pitch;
+            vo += vp;
+        };
+        int r = r0;
+        for (; r + 1 < r1; r += 2) {
+            row(r, a, b);
+            row(r + 1, b, a);
         }
+        if (r < r1) row(r, a, b);
         if (tag_prev >= 0 && own) {
             // the seeds 2 (h - d) of the sample the step before completed, in gauge
             // order, added to the depth adjoint just written at the gauge cells among
@@ -570,12 +611,13 @@ __global__ __launch_bounds__(kBlock) void k_adjv(const AdjvLaunch<T> A) {
                 const int gr = A.grc[2 * q], gc = A.grc[2 * q + 1];
                 if (gr < r0 || gr >= r1 || gc < xl || gc >= xl + V) continue;
                 const size_t cell = (size_t)gr * nx + gc;
-                const T hg = H[cell];
-                if (!clamp_mark(hg)) LHo[cell] += (T)(2.0 * ((double)hg - A.obs[(size_t)tag_prev * A.n_gauges + q]));
+                const T hg = H.p[cell];
+                if (!clamp_mark(hg)) const_cast<T*>(LHo.p)[cell] += (T)(2.0 * ((double)hg - A.obs[(size_t)tag_prev * A.n_gauges + q]));
             }
         }
         // rain-multiplier adjoint: the depth adjoint after the step summed over the
         // strip's cells, times R dt of the member's step
+        lsum = own ? lsum : 0.0;
         for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
         if (lane == 0) A.mubar_part[(size_t)(sy * C.strips_xa + sx) * C.n_members + k] += lsum * rdt;
     }
@@ -607,10 +649,7 @@ template <typename T> void launch_adjoint_march(const AdjvLaunch<T>& A, hipStrea
     const int nq = (C.n_members + 3) / 4;
     const dim3 grid(march_waves(C.strips_xa, C.strips_y, nq, C.march_order, C.march_bands));
     const size_t lds = (size_t)4 * C.march_rows * 64 * V * sizeof(T);
-    if (A.pf)
-        hipLaunchKernelGGL((k_adjv<T, V, 1>), grid, dim3(kBlock), lds, s, A);
-    else
-        hipLaunchKernelGGL((k_adjv<T, V, 0>), grid, dim3(kBlock), lds, s, A);
+    hipLaunchKernelGGL((k_adjv<T, V>), grid, dim3(kBlock), lds, s, A);
 }
 
 // One thread per member of the group (see launch_adj_segment); a cell seen by

@@ -290,6 +290,15 @@ __device__ __forceinline__ double lane_shr(double v, double fill) {
     return __hiloint2double(dpp_shr(__double2hiint(v), __double2hiint(fill)),
                             dpp_shr(__double2loint(v), __double2loint(fill)));
 }
+// the same shifts with zero entering
+__device__ __forceinline__ float lane_next(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_prev(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_next(double v) { return lane_shl(v, 0.0); }
+__device__ __forceinline__ double lane_prev(double v) { return lane_shr(v, 0.0); }
 // value i of four (0 for i outside 1..3)
 template <typename T> __device__ __forceinline__ T pick4(int i, T a, T b, T c, T d) {
     T v = a;

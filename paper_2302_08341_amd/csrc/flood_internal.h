@@ -318,7 +318,6 @@ template <typename T> struct AdjvLaunch {
     const double* obs;
     T* nacc;                  // [member quads][cell] Manning-field adjoint per quad of members (accumulated)
     double* mubar_part;       // [strips][group members] rain-multiplier adjoint partials (accumulated)
-    int32_t pf;               // 1: one row of load lookahead in the reverse march
 };
 template <typename T> void launch_adjoint_march(const AdjvLaunch<T>& A, hipStream_t s);
 template <typename T>

@@ -75,7 +75,6 @@ template <typename T> struct Impl : ImplBase {
     int march_nt = 1;         // non-temporal state streams in the vectorised row-marching kernel
     bool nt_forced = false;
     int march_xcd = 0;        // workgroup order of the vectorised row-marching kernel (see xcd_order)
-    int adj_pf = 0;           // the same in the adjoint's reverse march (off: 4.64 s against 4.15 s per C5 call)
     int total_waves = 0;      // waves of one row-marching launch
     int n_catch = 0, n_total = 0;
     std::vector<Cat> cats;
@@ -473,7 +472,6 @@ template <typename T> struct Impl : ImplBase {
             nt_forced = true;
         }
         if (const char* xc = std::getenv("FLOOD_MARCH_XCD")) march_xcd = std::min(4096, std::max(0, std::atoi(xc)));
-        if (const char* pf = std::getenv("FLOOD_ADJ_PF")) adj_pf = std::atoi(pf) ? 1 : 0;
         const char* ng = std::getenv("FLOOD_NO_GRAPH");
         use_graph = !(ng && ng[0] == '1');
         if (const char* gs = std::getenv("FLOOD_GRAPH_STEPS")) {   // steps per captured batch
@@ -1859,7 +1857,19 @@ template <typename T> struct Impl : ImplBase {
 // interleave, so its gradients do not depend on what the tuner picked.
 constexpr int kAdjTileRows = 4;
 constexpr int kAdjMarchRows = 8;
-constexpr int kAdjMarchOrder = 4;   // rows of strips in bands spread over the XCDs (see march_wave)
+constexpr int kAdjMarchOrder = 4;   // recorded forward, recomputation: strips in bands over the XCDs (see march_wave)
+// the reverse step: the member quads of a row of strips one after the other; at
+// 1024 x 1024 x 16 in FP32 128 us a step against 134 with order 4 and 132 with 0 or 2
+constexpr int kAdjReverseOrder = 3;
+// Rows per strip on grids too small to fill the chip: a strip is a chain of rows,
+// so strips are halved (down to 2 rows) while there are fewer of them than
+// workgroups to go round (`per` of them make one).  From the grid alone for the
+// reverse step, whose partial sums are taken by strip.  At 64 x 96 x 4 in FP64, 2
+// rows against 8: reverse step 11.0 us against 22.1, recorded step 8.4 against 14.9.
+static int adj_rows(int rows, int strips_x, int ny, int per) {
+    while (rows > 2 && strips_x * ((ny + rows - 1) / rows) < 256 * per) rows /= 2;
+    return rows;
+}
 constexpr size_t kAdjMaxGroup = 16;  // members of a row-march adjoint group at most
 
 // Members of a row-march adjoint group: as many as a pool of tape blocks holds
@@ -1896,7 +1906,8 @@ static CatchDev<T> group_view(const CatchDev<T>& C, int mi, int g0, int G, T* co
     // row-march geometry (members in planes), likewise fixed
     const int strip_w = 64 * march_vec<T>();       // the recorded forward and tape recomputation (k_marchv)
     const int strip_wa = 62 * adj_vec<T>();        // the reverse step (k_adjv)
-    int rows = kAdjMarchRows;   // at most 16: the reverse step stages 4 x rows x 64 x V values in LDS
+    // at most 16: the reverse step stages 4 x rows x 64 x V values in LDS
+    int rows = adj_rows(kAdjMarchRows, (C.nx + strip_wa - 1) / strip_wa, C.ny, 1);
     if (const char* ar = std::getenv("FLOOD_ADJ_ROWS")) rows = std::min(16, std::max(1, std::atoi(ar)));
     v.march_rows = std::min(rows, C.ny);
     v.strips_x = (C.nx + strip_w - 1) / strip_w;
@@ -1904,7 +1915,6 @@ static CatchDev<T> group_view(const CatchDev<T>& C, int mi, int g0, int G, T* co
     v.strips_y = (C.ny + v.march_rows - 1) / v.march_rows;
     v.wave_begin = 0;
     v.march_order = kAdjMarchOrder;
-    if (const char* ao = std::getenv("FLOOD_ADJ_ORDER")) v.march_order = std::min(4, std::max(0, std::atoi(ao)));
     // bands of about 1 MiB of bed and roughness, as in the forward (a multiple of 8)
     v.march_bands = std::max(8, std::min((int)std::ceil((double)C.ny * C.nx * 2.0 * sizeof(T) / (1 << 20) / 8.0) * 8,
                                          (v.strips_y + 7) / 8 * 8));
@@ -2305,6 +2315,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             CatchDev<T> TVF = TV;
             TVF.out_acc = V.out_acc;
             TVF.peak = V.peak;
+            set_march_rows(TVF, adj_rows(kAdjMarchRows, TVF.strips_x * Gg, C.ny, 4), Gg);
             if (const char* fr = std::getenv("FLOOD_ADJ_FROWS")) set_march_rows(TVF, std::max(1, std::atoi(fr)), Gg);
             CatchDev<T> TVR = TV;   // tape recomputation: the forward's geometry
             TVR.march_rows = TVF.march_rows;
@@ -2501,6 +2512,8 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             HIPCHK(hipMemsetAsync(d_lpar, 0, (size_t)Gi * sizeof(int32_t), st));
             HIPCHK(hipMemsetAsync(d_nacc, 0, (size_t)((Gg + 3) / 4) * ncell * sizeof(T), st));
             T* lb[2] = {lam, lam + slot_elems};
+            int rev_order = kAdjReverseOrder;
+            if (const char* ao = std::getenv("FLOOD_ADJ_ORDER")) rev_order = std::min(4, std::max(0, std::atoi(ao)));
             const int last_seg = (int)seg_nmax.size() - 1;
             for (int sg = last_seg; sg >= 0; --sg) {
                 const int nmax = seg_nmax[sg];
@@ -2527,6 +2540,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
                                       lb[0], lb[1], st);
                 AdjvLaunch<T> A{};
                 A.c = TV;
+                A.c.march_order = rev_order;
                 for (int w = 0; w < 2; ++w) {
                     A.lh[w] = lb[w];
                     A.lqx[w] = lb[w] + elemsG;
@@ -2545,7 +2559,6 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
                 A.obs = d_obs2;
                 A.nacc = d_nacc;
                 A.mubar_part = d_mubar;
-                A.pf = adj_pf;
                 for (int i = 0; i < nmax; ++i) {
                     A.i = i;
                     launch_adjoint_march<T>(A, st);
