@@ -220,7 +220,9 @@ flood_status flood_assimilate(flood_handle* h, int32_t catchment, int32_t n_gaug
  * planes, step kernel 3) keeps one state per member step in a pool of blocks
  * shared by the group, the tiled form ckpt_every + 1 states per member.  A
  * segment ends when a member has taken ckpt_every steps in it (or the pool
- * could run out), and the group's states become a checkpoint.  The reverse
+ * could run out), or, in the row-march form, earlier where that lets the steps
+ * still expected fit into one last segment; the group's states then become a
+ * checkpoint.  The reverse
  * sweep applies the discrete adjoint of the step with the recorded step
  * lengths and the forward's wet/dry, limiter and clamp branches held fixed:
  * the last segment straight from the tape, each earlier one after recomputing

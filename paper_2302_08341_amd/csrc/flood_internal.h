@@ -166,7 +166,7 @@ template <typename T> struct PlanLaunch {
     double* telog;            // optional [n_total][dtlog_cap] step end times
     int64_t* log_n;           // [n_total] steps logged since the log was opened (may exceed dtlog_cap)
     int32_t dtlog_cap;
-    double* dt_last;          // [n_total] length of each member's last step
+    double* dt_last;          // [n_total] Eq. 4 length of each member's last step (not cut to an event)
     const int64_t* step_lim;  // optional [n_total]: a member whose step count has reached it does not step
     int32_t m_begin, m_end;   // members planned by this launch (global indices)
     // adjoint record of this launch (null when not recording), indexed by m - m_begin
@@ -341,9 +341,12 @@ template <typename T>
 void launch_tape_gather(const CatchDev<T>& tape, const int32_t* blk, const CatchDev<T>& dst, const int32_t* dpar,
                         hipStream_t s);
 // [0] members of the group still short of t_end, [1] status word, [2] largest
-// seg_cnt, [3] tape blocks in use
+// seg_cnt, [3] the steps that the member furthest behind
+// still needs at its last step length dt[m] (0 before a first step), cut at the
+// samples s_t0 + k s_dt of which it has completed smp[m]
 void launch_count_group(int G, const double* t, const int32_t* fault, const double* t_end, const int32_t* status,
-                        const int32_t* seg_cnt, const int32_t* pool_next, int32_t* out, hipStream_t s);
+                        const int32_t* seg_cnt, const double* dt, const int32_t* smp, double s_t0, double s_dt,
+                        int32_t* out, hipStream_t s);
 template <typename T>
 void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s);
 template <typename T>

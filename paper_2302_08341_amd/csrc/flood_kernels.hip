@@ -120,6 +120,7 @@ __global__ __launch_bounds__(256) void k_plan(const PlanLaunch<T> P) {
     double tev = t_end < edge ? t_end : edge;
     const double ts = P.s_dt > 0.0 ? P.s_t0 + (double)(nsmp + 1) * P.s_dt : INFINITY;
     if (ts < tev) tev = ts;
+    const double dt_free = dt;   // not cut to an event
     double tn;
     if (dt >= tev - t) {
         dt = tev - t;
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(256) void k_plan(const PlanLaunch<T> P) {
         P.log_n[m] = li + 1;
     }
     P.t[m] = tn;
-    P.dt_last[m] = dt;
+    P.dt_last[m] = dt_free;
     P.par[m] = ms.parity ^ 1;
     P.steps[m] = st + 1;
     P.vrain[m] += (double)ms.rinc * C.ncells * (C.dx * C.dx);
@@ -441,36 +442,46 @@ void launch_count_active(int n_total, const double* t, const int32_t* fault, con
 
 __global__ __launch_bounds__(256) void k_count_group(int n, const double* t, const int32_t* fault,
                                                      const double* t_end, const int32_t* status,
-                                                     const int32_t* seg_cnt, const int32_t* pool_next,
+                                                     const int32_t* seg_cnt, const double* dt, const int32_t* smp,
+                                                     double s_t0, double s_dt,
                                                      int32_t* out) {
-    __shared__ int part[4], mpart[4];
-    int c = 0, mx = 0;
+    __shared__ int part[4], mpart[4], npart[4];
+    int c = 0, mx = 0, need = 0;
     const double te = *t_end;
     for (int m = threadIdx.x; m < n; m += 256) {
-        c += (!fault[m] && t[m] < te) ? 1 : 0;
         mx = max(mx, seg_cnt[m]);
+        if (fault[m] || !(t[m] < te)) continue;
+        ++c;
+        if (!(dt[m] > 0.0)) continue;
+        // to the member's next sample, then whole sample intervals, at its last step length
+        const double ts = fmin(s_t0 + (double)(smp[m] + 1) * s_dt, te);
+        const double k = ceil((ts - t[m]) / dt[m]) + rint((te - ts) / s_dt) * ceil(s_dt / dt[m]);
+        need = max(need, (int)fmin(k, 1e9));
     }
     for (int off = 32; off > 0; off >>= 1) {
         c += __shfl_xor(c, off, 64);
         mx = max(mx, __shfl_xor(mx, off, 64));
+        need = max(need, __shfl_xor(need, off, 64));
     }
     if ((threadIdx.x & 63) == 0) {
         part[threadIdx.x >> 6] = c;
         mpart[threadIdx.x >> 6] = mx;
+        npart[threadIdx.x >> 6] = need;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         out[0] = part[0] + part[1] + part[2] + part[3];
         out[1] = status[0];
         out[2] = max(max(mpart[0], mpart[1]), max(mpart[2], mpart[3]));
-        out[3] = *pool_next;
+        out[3] = max(max(npart[0], npart[1]), max(npart[2], npart[3]));
     }
 }
 
 void launch_count_group(int G, const double* t, const int32_t* fault, const double* t_end, const int32_t* status,
-                        const int32_t* seg_cnt, const int32_t* pool_next, int32_t* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_count_group, dim3(1), dim3(256), 0, s, G, t, fault, t_end, status, seg_cnt, pool_next,
-                       out);
+                        const int32_t* seg_cnt, const double* dt, const int32_t* smp, double s_t0, double s_dt,
+                        int32_t* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_count_group, dim3(1), dim3(256), 0, s, G, t, fault, t_end, status, seg_cnt, dt, smp, s_t0,
+                       s_dt, out);
 }
 
 __global__ __launch_bounds__(256) void k_step_limit(int n, const int64_t* steps, int64_t add, int64_t* lim) {

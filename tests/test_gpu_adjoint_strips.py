@@ -56,3 +56,14 @@ def test_rows_per_strip(fl, monkeypatch, rows):
     monkeypatch.setenv("FLOOD_ADJ_ROWS", str(rows))
     monkeypatch.setenv("FLOOD_ADJ_FROWS", str(rows))
     _close(_run(fl, 35, 128, (1, 1, 1, 1), 8, 3, 100), ref, 1e-10)
+
+
+@pytest.mark.parametrize("ckpt", [1, 2, 3, 7, 8, 9, 17, 30, 45])
+def test_ends_of_the_tape_segments(fl, ckpt):
+    # wherever the segments end, the loss and the rain-multiplier gradients are those
+    # of the whole window in one segment, bit for bit
+    ref = _run(fl, 24, 64, (1, 1, 1, 1), 8, 3, 1000)
+    got = _run(fl, 24, 64, (1, 1, 1, 1), 8, 3, ckpt)
+    assert got[0] == ref[0]
+    np.testing.assert_array_equal(got[2], ref[2])
+    assert np.linalg.norm(got[1] - ref[1]) <= 1e-10 * np.linalg.norm(ref[1])
