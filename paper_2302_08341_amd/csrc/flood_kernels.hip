@@ -575,34 +575,50 @@ void launch_hmax_init(int mi, const CatchDev<T>& C, const int32_t* par, typename
 }
 
 // Storage sum(h) dx^2 per member, added into out[member] (out must be zero).
-template <typename T, int MI>
-__global__ __launch_bounds__(256) void k_storage(const CatchDev<T> C, const int32_t* par, double* out) {
+// Bound by the read of the depths.  A few workgroups per member, each over many
+// cells: their sums meet in atomics on one or two cache lines, about 20 ns apiece,
+// and with one workgroup per 256 cells those were the whole time (1024 x 1024 x 16:
+// 320 us then, 46 now; 2000 x 2000 x 96: 725, 257, 6.0 TB/s).  Four independent partial sums per thread; cells of a member lie
+// `mi` apart.
+template <typename T, int V>
+__global__ __launch_bounds__(256) void k_storage(const CatchDev<T> C, int mi, const int32_t* par, double* out) {
     const int m = blockIdx.y;
     const size_t ncell = (size_t)C.ny * C.nx;
-    const T* h = C.h[par[C.member_off + m]];
-    double acc = 0.0;
-    for (size_t cell = (size_t)blockIdx.x * blockDim.x + threadIdx.x; cell < ncell;
-         cell += (size_t)gridDim.x * blockDim.x) {
-        const int r = (int)(cell / C.nx), c = (int)(cell % C.nx);
-        acc += (double)h[state_index<T, MI>(C, m, r, c)];
+    const T* h = C.h[par[C.member_off + m]] + (size_t)(m / mi) * ncell * mi + m % mi;
+    double acc[V] = {};
+    const size_t nv = V == 1 ? ncell : ncell / V;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < nv; e += stride) {
+        if constexpr (V > 1) {
+            T v[V];
+            vload<T, V>(h + e * V, v);
+#pragma unroll
+            for (int j = 0; j < V; ++j) acc[j] += (double)v[j];
+        } else {
+            acc[0] += (double)h[e * mi];
+        }
     }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    double sum = 0.0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) sum += acc[j];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
     __shared__ double part[4];
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(out + m, ((part[0] + part[1]) + (part[2] + part[3])) * (C.dx * C.dx));
 }
 
 template <typename T>
 void launch_storage(int mi, const CatchDev<T>& C, const int32_t* par, double* out, hipStream_t s) {
+    constexpr int V = march_vec<T>();
     const size_t ncell = (size_t)C.ny * C.nx;
-    dim3 grid((unsigned)std::min<size_t>((ncell + 255) / 256, 1024), C.n_members);
-    switch (mi) {
-        case 1: hipLaunchKernelGGL((k_storage<T, 1>), grid, dim3(256), 0, s, C, par, out); break;
-        case 2: hipLaunchKernelGGL((k_storage<T, 2>), grid, dim3(256), 0, s, C, par, out); break;
-        case 4: hipLaunchKernelGGL((k_storage<T, 4>), grid, dim3(256), 0, s, C, par, out); break;
-        default: hipLaunchKernelGGL((k_storage<T, 8>), grid, dim3(256), 0, s, C, par, out); break;
-    }
+    // whole vectors of cells in every member's plane
+    const bool vec = mi == 1 && ncell % V == 0;
+    const size_t per = (ncell / (vec ? V : 1) + 255) / 256;
+    const size_t want = (size_t)std::max(8, 4096 / C.n_members);
+    dim3 grid((unsigned)std::max<size_t>(1, std::min(per, want)), C.n_members);
+    if (vec) hipLaunchKernelGGL((k_storage<T, V>), grid, dim3(256), 0, s, C, mi, par, out);
+    else hipLaunchKernelGGL((k_storage<T, 1>), grid, dim3(256), 0, s, C, mi, par, out);
 }
 
 // One member's field in the host layout (H: ny*nx, QX: ny*(nx+1), QY: (ny+1)*nx).
