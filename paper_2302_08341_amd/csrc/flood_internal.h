@@ -268,10 +268,13 @@ void launch_sections(int mi, const CatchDev<T>& C, const int32_t* par, int n_sec
                      const int32_t* code, const int32_t* index, double* out, int out_stride, int out_off,
                      hipStream_t s);
 void launch_flush_outflow(int n_members, int nb, double* out_acc, double* vout, hipStream_t s);
-// ensemble products of the running maximum depth: prob [ny*nx], pct [n_pct][ny*nx]
+// ensemble products of the running maximum depth over cells [cell0, cell0 + count):
+// prob [count], pct maps [n_pct][count]; prob may be null.  w: member weights,
+// followed by zeros up to kProdPad entries
+constexpr int kProdPad = 128;
 template <typename T>
 void launch_products(int mi, const CatchDev<T>& C, double threshold, int n_pct, const double* pct, const double* w,
-                     double W, double* prob, double* pct_out, hipStream_t s);
+                     double W, size_t cell0, size_t count, double* prob, double* pout, hipStream_t s);
 
 // adjoint (flood_adjoint.hip)
 template <typename T> struct AdjLaunch {

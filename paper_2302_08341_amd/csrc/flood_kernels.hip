@@ -1817,44 +1817,176 @@ template void launch_march<double>(const StepLaunch<double>&, int, int, hipStrea
 
 
 // ---------------------------------------------------------------------------
-// Ensemble products of the running maximum depth (Sec. 4.4, Figs. 15-16).  A
-// workgroup covers 64 cells with four wavefronts, one lane per cell in each:
-// it stages its cells' member values in LDS (member-major, so the staging
-// loads are contiguous in every member's plane), the first wavefront forms, in
-// member order and FP64, the weight of the members at or above the threshold,
-// and the four wavefronts share the candidates k: for each, the weight of the
-// members at or below member k's value, again in member order; the smallest
-// value whose weight reaches p W is the p-quantile (inverted distribution
-// function), a minimum over the candidates that is the same in any order.
-// ---------------------------------------------------------------------------
+// Ensemble products of the running maximum depth (Sec. 4.4, Figs. 15-16): the
+// weight of the members at or above the threshold, and for each p the smallest
+// member value v_k whose weight, that of the members at or below it, reaches p W
+// (inverted distribution function).  Every weight is summed in FP64 in member
+// order.
+//
+// One wavefront covers 64 cells, a lane each.  A weight summed that way never
+// falls when members join the sum (a rounded addition keeps the order of its
+// operands), so it never falls along the sorted values, and the first value that
+// reaches p W is found by bisection: the values of a cell are sorted in registers
+// (odd-even merges) into LDS, read again into the registers in member order, and
+// each of log2(NP) rounds forms the exact weight of one candidate per percentile.
+// In the sort a NaN (of a member that failed) stands as infinity, the value of a
+// percentile that no candidate reaches.  Bound by the compares, selects and FMAs
+// of the rounds: 18 per member and percentile at 64 members, where every
+// candidate's weight took 3 x 64.  Three percentiles in FP32: 512 x 512 x 64 63 us from 212,
+// 256 x 256 x 128 47 from 162; in FP64 256 x 256 x 64 24 from 39.
+// NP: members, rounded up to a power of two.  The registers hold NP values, so
+// ensembles past 128 members (64 in FP64) take k_products_any.
+// Cells [cell0, cell0 + count) of the grid: prob [count], pout [n_pct][count].
+template <typename T> constexpr T kInf = std::numeric_limits<T>::infinity();
+
+template <typename T> __device__ __forceinline__ void sort_pair(T& a, T& b) {
+    T lo, hi;
+    if constexpr (sizeof(T) == 4) {
+        lo = __builtin_fminf(a, b);
+        hi = __builtin_fmaxf(a, b);
+    } else {
+        lo = __builtin_fmin(a, b);
+        hi = __builtin_fmax(a, b);
+    }
+    a = lo;
+    b = hi;
+}
+
+// Batcher's odd-even merge sort of v[LO .. LO + N), ascending
+template <int LO, int N, int R, typename T, int NP> __device__ __forceinline__ void merge_odd_even(T (&v)[NP]) {
+    if constexpr (2 * R < N) {
+        merge_odd_even<LO, N, 2 * R>(v);
+        merge_odd_even<LO + R, N, 2 * R>(v);
+#pragma unroll
+        for (int i = LO + R; i + R < LO + N; i += 2 * R) sort_pair(v[i], v[i + R]);
+    } else {
+        sort_pair(v[LO], v[LO + R]);
+    }
+}
+template <int LO, int N, typename T, int NP> __device__ __forceinline__ void sort_odd_even(T (&v)[NP]) {
+    if constexpr (N > 1) {
+        sort_odd_even<LO, N / 2>(v);
+        sort_odd_even<LO + N / 2, N / 2>(v);
+        merge_odd_even<LO, N, 1>(v);
+    }
+}
+
+// Bisection of G percentiles at once.  v: the cell's values in member order, w:
+// weights, zero past the last member; sorted: the values in ascending order, the
+// last of which always reaches (all of W, or infinity).
+template <int G, typename T, int NP>
+__device__ __forceinline__ void find_percentiles(const T (&v)[NP], const T* sorted, int lane, const double* __restrict__ w,
+                                                 const double* __restrict__ pct, double W, double (&out)[3]) {
+    int pos[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) pos[i] = 0;
+    for (int half = NP / 2; half >= 1; half /= 2) {
+        T p[G];
+        double cum[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            p[i] = sorted[(pos[i] + half - 1) * 64 + lane];
+            cum[i] = 0.0;
+        }
+        // w_m x 1 or x 0 in one FMA: the sum of the selected weights, rounded as the
+        // plain additions are (weights are finite and >= 0)
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const double wm = w[m];
+#pragma unroll
+            for (int i = 0; i < G; ++i) cum[i] = __builtin_fma(wm, v[m] <= p[i] ? 1.0 : 0.0, cum[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+            if (p[i] < kInf<T> && !(cum[i] >= pct[i] * W)) pos[i] += half;
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i) out[i] = (double)sorted[pos[i] * 64 + lane];
+}
+
+template <typename T, int NP>
+__global__ __launch_bounds__(64) void k_products(const CatchDev<T> C, int mi, double thr, int n_pct,
+                                                 const double* __restrict__ pct, const double* __restrict__ w,
+                                                 double W, size_t cell0, size_t count, double* __restrict__ prob,
+                                                 double* __restrict__ pout) {
+    __shared__ T sorted[NP * 64];
+    const int lane = threadIdx.x;
+    const size_t i = (size_t)blockIdx.x * 64 + lane;
+    const size_t ncell = (size_t)C.ny * C.nx;
+    const T* at = C.peak + (cell0 + (i < count ? i : count - 1)) * mi;
+    const int N = C.n_members;
+    // member m's value (mi, a power of two, members interleaved); places past the
+    // last member read that one's
+    auto value = [&](int m) -> T {
+        const int k = m < N ? m : N - 1;
+        return at[(size_t)(k & ~(mi - 1)) * ncell + (k & (mi - 1))];
+    };
+    T v[NP];
+#pragma unroll
+    for (int m = 0; m < NP; ++m) v[m] = value(m);
+    if (n_pct > 0) {
+#pragma unroll
+        for (int m = 0; m < NP; ++m) v[m] = m < N && v[m] == v[m] ? v[m] : kInf<T>;
+        sort_odd_even<0, NP>(v);
+#pragma unroll
+        for (int m = 0; m < NP; ++m) sorted[m * 64 + lane] = v[m];
+        __asm__ volatile("" ::: "memory");   // loads again, from the caches, instead of twice the registers
+#pragma unroll
+        for (int m = 0; m < NP; ++m) v[m] = value(m);
+    }
+    if (prob) {
+        double hit = 0.0;
+#pragma unroll
+        for (int m = 0; m < NP; ++m) hit = __builtin_fma(w[m], (double)v[m] >= thr ? 1.0 : 0.0, hit);
+        if (i < count) prob[i] = hit / W;
+    }
+    double q[3];
+    for (int p = 0; p < n_pct; p += 3) {
+        const int g = n_pct - p;
+        if (g >= 3) find_percentiles<3>(v, sorted, lane, w, pct + p, W, q);
+        else if (g == 2) find_percentiles<2>(v, sorted, lane, w, pct + p, W, q);
+        else find_percentiles<1>(v, sorted, lane, w, pct + p, W, q);
+        if (i >= count) continue;
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < g) pout[(size_t)(p + e) * count + i] = q[e];
+    }
+}
+
+// The same for any number of members.  A workgroup covers 64 cells with four
+// wavefronts, one lane per cell in each: it stages its cells' member values in LDS
+// where they fit, the first wavefront forms the weight of the members at or above
+// the threshold, and the four share the candidates k: for each, the weight of the
+// members at or below member k's value; the smallest value whose weight reaches
+// p W is a minimum over the candidates that is the same in any order.
 constexpr int kProdCells = 64;
 constexpr int kProdWaves = 4;      // wavefronts per workgroup, splitting the candidates
 constexpr int kProdMaxPct = 16;
 
 constexpr int kProdUnroll = 8;   // percentile candidates evaluated per pass over the members
 
-template <typename T, int MI, bool LDS>
-__global__ __launch_bounds__(kProdCells * kProdWaves) void k_products(const CatchDev<T> C, double thr, int n_pct,
-                                                                       const double* __restrict__ pct,
-                                                                       const double* __restrict__ w, double W,
-                                                                       double* __restrict__ prob,
-                                                                       double* __restrict__ pout) {
+template <typename T, bool LDS>
+__global__ __launch_bounds__(kProdCells * kProdWaves) void k_products_any(
+    const CatchDev<T> C, int mi, double thr, int n_pct, const double* __restrict__ pct, const double* __restrict__ w,
+    double W, size_t cell0, size_t count, double* __restrict__ prob, double* __restrict__ pout) {
     extern __shared__ unsigned char smem[];
     T* vals = reinterpret_cast<T*>(smem);
     const int N = C.n_members;
     const size_t ncell = (size_t)C.ny * C.nx;
     const int lane = (int)threadIdx.x % kProdCells;
     const int wave = (int)threadIdx.x / kProdCells;
-    const size_t cell = (size_t)blockIdx.x * kProdCells + lane;
-    const bool in = cell < ncell;
-    const int r = in ? (int)(cell / C.nx) : 0, c = in ? (int)(cell % C.nx) : 0;
+    const size_t cell = (size_t)blockIdx.x * kProdCells + lane;   // of this range
+    const bool in = cell < count;
+    auto peak = [&](int m) -> T {
+        return C.peak[(size_t)(m / mi) * ncell * mi + (cell0 + (in ? cell : 0)) * mi + m % mi];
+    };
     auto value = [&](int m) -> T {
         if constexpr (LDS) return vals[(size_t)m * kProdCells + lane];
-        else return C.peak[state_index<T, MI>(C, m, r, c)];
+        else return peak(m);
     };
     if constexpr (LDS) {
         for (int m = wave; m < N; m += kProdWaves)
-            vals[(size_t)m * kProdCells + lane] = in ? C.peak[state_index<T, MI>(C, m, r, c)] : T(0);
+            vals[(size_t)m * kProdCells + lane] = in ? peak(m) : T(0);
     }
     __syncthreads();
     const bool want_pct = n_pct > 0 && pout != nullptr;   // the same for the whole grid
@@ -1912,39 +2044,41 @@ __global__ __launch_bounds__(kProdCells * kProdWaves) void k_products(const Catc
                 const double o = red[((size_t)v * n_pct + i) * kProdCells + lane];
                 b = o < b ? o : b;
             }
-            pout[(size_t)i * ncell + cell] = b;
+            pout[(size_t)i * count + cell] = b;
         }
 }
 
-template <typename T, int MI>
-static void launch_products_mi(const CatchDev<T>& C, double thr, int n_pct, const double* pct, const double* w,
-                               double W, double* prob, double* pout, hipStream_t s) {
-    const size_t ncell = (size_t)C.ny * C.nx;
-    const dim3 grid((unsigned)((ncell + kProdCells - 1) / kProdCells));
-    const dim3 block(kProdCells * kProdWaves);
-    const size_t stage = (size_t)C.n_members * kProdCells * sizeof(T);
-    const size_t red = (size_t)kProdWaves * std::max(n_pct, 1) * kProdCells * sizeof(double);
-    if (stage <= 48 * 1024)
-        hipLaunchKernelGGL((k_products<T, MI, true>), grid, block, std::max(stage, red), s, C, thr, n_pct, pct, w, W,
-                           prob, pout);
-    else
-        hipLaunchKernelGGL((k_products<T, MI, false>), grid, block, red, s, C, thr, n_pct, pct, w, W, prob, pout);
+template <typename T, int NP>
+static void launch_products_np(int mi, const CatchDev<T>& C, double thr, int n_pct, const double* pct, const double* w,
+                               double W, size_t cell0, size_t count, double* prob, double* pout, hipStream_t s) {
+    hipLaunchKernelGGL((k_products<T, NP>), dim3((unsigned)((count + 63) / 64)), dim3(64), 0, s, C, mi, thr, n_pct, pct,
+                       w, W, cell0, count, prob, pout);
 }
 
 template <typename T>
 void launch_products(int mi, const CatchDev<T>& C, double thr, int n_pct, const double* pct, const double* w,
-                     double W, double* prob, double* pout, hipStream_t s) {
-    switch (mi) {
-        case 1: launch_products_mi<T, 1>(C, thr, n_pct, pct, w, W, prob, pout, s); break;
-        case 2: launch_products_mi<T, 2>(C, thr, n_pct, pct, w, W, prob, pout, s); break;
-        case 4: launch_products_mi<T, 4>(C, thr, n_pct, pct, w, W, prob, pout, s); break;
-        default: launch_products_mi<T, 8>(C, thr, n_pct, pct, w, W, prob, pout, s); break;
-    }
+                     double W, size_t cell0, size_t count, double* prob, double* pout, hipStream_t s) {
+    const int N = C.n_members;
+    if (N <= 16) return launch_products_np<T, 16>(mi, C, thr, n_pct, pct, w, W, cell0, count, prob, pout, s);
+    if (N <= 32) return launch_products_np<T, 32>(mi, C, thr, n_pct, pct, w, W, cell0, count, prob, pout, s);
+    if (N <= 64) return launch_products_np<T, 64>(mi, C, thr, n_pct, pct, w, W, cell0, count, prob, pout, s);
+    if constexpr (sizeof(T) == 4)
+        if (N <= 128) return launch_products_np<T, 128>(mi, C, thr, n_pct, pct, w, W, cell0, count, prob, pout, s);
+    const dim3 grid((unsigned)((count + kProdCells - 1) / kProdCells));
+    const dim3 block(kProdCells * kProdWaves);
+    const size_t stage = (size_t)N * kProdCells * sizeof(T);
+    const size_t red = (size_t)kProdWaves * std::max(n_pct, 1) * kProdCells * sizeof(double);
+    if (stage <= 48 * 1024)
+        hipLaunchKernelGGL((k_products_any<T, true>), grid, block, std::max(stage, red), s, C, mi, thr, n_pct, pct, w, W,
+                           cell0, count, prob, pout);
+    else
+        hipLaunchKernelGGL((k_products_any<T, false>), grid, block, red, s, C, mi, thr, n_pct, pct, w, W, cell0, count,
+                           prob, pout);
 }
 
 template void launch_products<float>(int, const CatchDev<float>&, double, int, const double*, const double*, double,
-                                     double*, double*, hipStream_t);
+                                     size_t, size_t, double*, double*, hipStream_t);
 template void launch_products<double>(int, const CatchDev<double>&, double, int, const double*, const double*, double,
-                                      double*, double*, hipStream_t);
+                                      size_t, size_t, double*, double*, hipStream_t);
 
 }  // namespace flood

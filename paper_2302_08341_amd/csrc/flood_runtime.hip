@@ -1737,13 +1737,14 @@ template <typename T> struct Impl : ImplBase {
             return FLOOD_OK;
         };
         double *d_w, *d_p, *d_prob = nullptr, *d_out = nullptr;
-        CHK(talloc(C.N * sizeof(double), (void**)&d_w));
+        w.resize(std::max(C.N, kProdPad), 0.0);
+        CHK(talloc(w.size() * sizeof(double), (void**)&d_w));
         CHK(talloc(16 * sizeof(double), (void**)&d_p));
         if (prob_out) CHK(talloc(ncell * sizeof(double), (void**)&d_prob));
         if (pct_out && n_pct > 0) CHK(talloc((size_t)n_pct * ncell * sizeof(double), (void**)&d_out));
-        HIPCHK(hipMemcpyAsync(d_w, w.data(), C.N * sizeof(double), hipMemcpyHostToDevice, st));
+        HIPCHK(hipMemcpyAsync(d_w, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice, st));
         if (n_pct > 0) HIPCHK(hipMemcpyAsync(d_p, pct, n_pct * sizeof(double), hipMemcpyHostToDevice, st));
-        launch_products<T>(mi, C.dev, threshold, d_out ? n_pct : 0, d_p, d_w, W, d_prob, d_out, st);
+        launch_products<T>(mi, C.dev, threshold, d_out ? n_pct : 0, d_p, d_w, W, 0, ncell, d_prob, d_out, st);
         HIPCHK(hipGetLastError());
         if (d_prob) HIPCHK(hipMemcpyAsync(prob_out, d_prob, ncell * sizeof(double), hipMemcpyDeviceToHost, st));
         if (d_out)
