@@ -251,11 +251,17 @@ void launch_hmax_init(int mi, const CatchDev<T>& C, const int32_t* par, typename
 template <typename T>
 void launch_storage(int mi, const CatchDev<T>& C, const int32_t* par, double* out, hipStream_t s);
 template <typename T>
-void launch_get_field(int mi, const CatchDev<T>& C, int member, int par, int which, double* out,
-                      hipStream_t s);
+void launch_get_field(int mi, const CatchDev<T>& C, int member, const int32_t* par, int which, size_t e0, size_t count,
+                      double* out, hipStream_t s);
 template <typename T>
-void launch_set_field(int mi, const CatchDev<T>& C, int member, int par, int which, const double* in,
+void launch_set_field(int mi, const CatchDev<T>& C, int member, const int32_t* par, int which, const double* in,
                       hipStream_t s);
+// up to 8 arrays of n 8-byte values, one after another in dst
+struct PackList {
+    const uint64_t* src[8];
+    int32_t arrays, n;
+};
+void launch_pack(const PackList& L, uint64_t* dst, hipStream_t s);
 template <typename T>
 void launch_gauges(int mi, const CatchDev<T>& C, const int32_t* par, int n_gauges, const int32_t* grc,
                    double* y, int y_stride, hipStream_t s);

@@ -621,59 +621,59 @@ void launch_storage(int mi, const CatchDev<T>& C, const int32_t* par, double* ou
     else hipLaunchKernelGGL((k_storage<T, 1>), grid, dim3(256), 0, s, C, mi, par, out);
 }
 
-// One member's field in the host layout (H: ny*nx, QX: ny*(nx+1), QY: (ny+1)*nx).
-template <typename T, int MI>
-__global__ __launch_bounds__(256) void k_field(const CatchDev<T> C, int m, int p, int which, double* buf,
-                                               int to_state) {
+// Elements [e0, e0 + count) of one member's field in the host layout (H: ny*nx, QX:
+// ny*(nx+1), QY: (ny+1)*nx), buf[0] the first of them.  The member's current copy is
+// read from par (null: copy 0).
+template <typename T>
+__global__ __launch_bounds__(256) void k_field(const CatchDev<T> C, int mi, int m, const int32_t* par, int which,
+                                               size_t e0, size_t count, double* buf, int to_state) {
     const int ny = C.ny, nx = C.nx;
-    const size_t n = (which == 0 || which == 3) ? (size_t)ny * nx
-                     : which == 1               ? (size_t)ny * (nx + 1)
-                                                : (size_t)(ny + 1) * nx;
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const int k = m / MI, lane = m % MI;
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= count) return;
+    const int p = par ? par[C.member_off + m] : 0;
+    const size_t e = e0 + i;
+    const size_t k = m / mi, lane = m % mi, ncell = (size_t)ny * nx;
+    auto at = [&](T* base, size_t cell) { return base + (k * ncell + cell) * mi + lane; };
     T* ptr;
     if (which == 3) {
-        ptr = C.peak + state_index<T, MI>(C, m, (int)(e / nx), (int)(e % nx));
+        ptr = at(C.peak, e);
     } else if (which == 0) {
-        ptr = C.h[p] + state_index<T, MI>(C, m, (int)(e / nx), (int)(e % nx));
+        ptr = at(C.h[p], e);
     } else if (which == 1) {
-        const int r = (int)(e / (nx + 1)), c = (int)(e % (nx + 1));
-        ptr = (c == 0) ? C.qw[p] + ((size_t)k * ny + r) * MI + lane : C.qx[p] + state_index<T, MI>(C, m, r, c - 1);
+        const size_t r = e / (nx + 1), c = e % (nx + 1);
+        ptr = c == 0 ? C.qw[p] + (k * ny + r) * mi + lane : at(C.qx[p], r * nx + c - 1);
     } else {
-        const int r = (int)(e / nx), c = (int)(e % nx);
-        ptr = (r == 0) ? C.qn[p] + ((size_t)k * nx + c) * MI + lane : C.qy[p] + state_index<T, MI>(C, m, r - 1, c);
+        ptr = e < (size_t)nx ? C.qn[p] + (k * nx + e) * mi + lane : at(C.qy[p], e - nx);
     }
     if (to_state)
-        *ptr = (T)buf[e] + T(0);
+        *ptr = (T)buf[i] + T(0);
     else
-        buf[e] = (double)*ptr;
+        buf[i] = (double)*ptr;
 }
 
 template <typename T>
-static void launch_field(int mi, const CatchDev<T>& C, int member, int par, int which, double* buf, int to_state,
-                         hipStream_t s) {
-    const int ny = C.ny, nx = C.nx;
-    const size_t n = (which == 0 || which == 3) ? (size_t)ny * nx
-                     : which == 1               ? (size_t)ny * (nx + 1)
-                                                : (size_t)(ny + 1) * nx;
-    dim3 grid((unsigned)((n + 255) / 256));
-    switch (mi) {
-        case 1: hipLaunchKernelGGL((k_field<T, 1>), grid, dim3(256), 0, s, C, member, par, which, buf, to_state); break;
-        case 2: hipLaunchKernelGGL((k_field<T, 2>), grid, dim3(256), 0, s, C, member, par, which, buf, to_state); break;
-        case 4: hipLaunchKernelGGL((k_field<T, 4>), grid, dim3(256), 0, s, C, member, par, which, buf, to_state); break;
-        default: hipLaunchKernelGGL((k_field<T, 8>), grid, dim3(256), 0, s, C, member, par, which, buf, to_state); break;
-    }
-}
-
-template <typename T>
-void launch_get_field(int mi, const CatchDev<T>& C, int member, int par, int which, double* out, hipStream_t s) {
-    launch_field<T>(mi, C, member, par, which, out, 0, s);
+void launch_get_field(int mi, const CatchDev<T>& C, int member, const int32_t* par, int which, size_t e0, size_t count,
+                      double* out, hipStream_t s) {
+    hipLaunchKernelGGL((k_field<T>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, C, mi, member, par, which,
+                       e0, count, out, 0);
 }
 template <typename T>
-void launch_set_field(int mi, const CatchDev<T>& C, int member, int par, int which, const double* in,
+void launch_set_field(int mi, const CatchDev<T>& C, int member, const int32_t* par, int which, const double* in,
                       hipStream_t s) {
-    launch_field<T>(mi, C, member, par, which, const_cast<double*>(in), 1, s);
+    const size_t n = (which == 0 || which == 3) ? (size_t)C.ny * C.nx
+                     : which == 1               ? (size_t)C.ny * (C.nx + 1)
+                                                : (size_t)(C.ny + 1) * C.nx;
+    hipLaunchKernelGGL((k_field<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, C, mi, member, par, which, 0, n,
+                       const_cast<double*>(in), 1);
+}
+
+__global__ __launch_bounds__(256) void k_pack(const PackList L, uint64_t* dst) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < L.n) dst[(size_t)blockIdx.y * L.n + i] = L.src[blockIdx.y][i];
+}
+
+void launch_pack(const PackList& L, uint64_t* dst, hipStream_t s) {
+    hipLaunchKernelGGL(k_pack, dim3((L.n + 255) / 256, L.arrays), dim3(256), 0, s, L, dst);
 }
 
 // Wet/dry decision of every link of member m from its state in copy p, in the
@@ -833,10 +833,12 @@ template void launch_hmax_init<double>(int, const CatchDev<double>&, const int32
                                        hipStream_t);
 template void launch_storage<float>(int, const CatchDev<float>&, const int32_t*, double*, hipStream_t);
 template void launch_storage<double>(int, const CatchDev<double>&, const int32_t*, double*, hipStream_t);
-template void launch_get_field<float>(int, const CatchDev<float>&, int, int, int, double*, hipStream_t);
-template void launch_get_field<double>(int, const CatchDev<double>&, int, int, int, double*, hipStream_t);
-template void launch_set_field<float>(int, const CatchDev<float>&, int, int, int, const double*, hipStream_t);
-template void launch_set_field<double>(int, const CatchDev<double>&, int, int, int, const double*, hipStream_t);
+template void launch_get_field<float>(int, const CatchDev<float>&, int, const int32_t*, int, size_t, size_t, double*,
+                                     hipStream_t);
+template void launch_get_field<double>(int, const CatchDev<double>&, int, const int32_t*, int, size_t, size_t, double*,
+                                      hipStream_t);
+template void launch_set_field<float>(int, const CatchDev<float>&, int, const int32_t*, int, const double*, hipStream_t);
+template void launch_set_field<double>(int, const CatchDev<double>&, int, const int32_t*, int, const double*, hipStream_t);
 template void launch_wetmask<float>(int, const CatchDev<float>&, int, int, uint8_t*, uint8_t*, hipStream_t);
 template void launch_wetmask<double>(int, const CatchDev<double>&, int, int, uint8_t*, uint8_t*, hipStream_t);
 template void launch_gauges<float>(int, const CatchDev<float>&, const int32_t*, int, const int32_t*, double*, int,

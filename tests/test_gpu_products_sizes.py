@@ -49,3 +49,21 @@ def test_products_of_any_member_count(fl, orc, N, n_pct, rb, mi):
         rp, rpc = orc.ensemble_products(peaks, 0.3, PCT[:n_pct], weights=wf)
         np.testing.assert_array_equal(prob, rp)
         np.testing.assert_array_equal(pc, np.stack(rpc))
+
+
+@pytest.mark.parametrize("ny,nx", [(512, 512), (513, 512), (1100, 1000)])
+def test_fields_larger_than_the_staging_slots(fl, ny, nx):
+    # a slot holds 512 x 512 values, the ring three slots
+    rng = np.random.default_rng(ny)
+    cat = dict(dem=np.zeros((ny, nx), np.float32), manning=np.full((ny, nx), 0.03, np.float32), dx=2.0,
+               edge_kind=(1, 1, 1, 1), edge_slope=(1e-3,) * 4, n_members=2, n_scale=np.ones(2), rain_mult=np.ones(2),
+               h0=np.zeros((ny, nx), np.float32))
+    e = fl.FloodEnsemble([cat], np.array([1e-6]), real_bytes=8, member_interleave=1, track_peak=True)
+    h, qx, qy = rng.uniform(0, 1, (ny, nx)), rng.uniform(0, 1, (ny, nx + 1)), rng.uniform(0, 1, (ny + 1, nx))
+    e.set_state(1, h, qx, qy, 0.0)
+    for which, want in ((fl.FIELD_H, h), (fl.FIELD_QX, qx), (fl.FIELD_QY, qy), (fl.FIELD_PEAK, h)):
+        np.testing.assert_array_equal(e.field(1, which), want)
+    prob, pc = e.products(0.5, PCT[:3])
+    np.testing.assert_array_equal(prob, (h >= 0.5) / 2.0)
+    np.testing.assert_array_equal(pc[2], h)          # p = 1: the larger of 0 and h
+    np.testing.assert_array_equal(pc[1], 0.0 * h)
