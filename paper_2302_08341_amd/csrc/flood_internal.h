@@ -256,6 +256,20 @@ void launch_get_field(int mi, const CatchDev<T>& C, int member, const int32_t* p
 template <typename T>
 void launch_set_field(int mi, const CatchDev<T>& C, int member, const int32_t* par, int which, const double* in,
                       hipStream_t s);
+// Up to kCopyList arrays (whole 4-byte words) copied in one launch, and *clear, if
+// given, set to zero.  The caller fills dst, src and bytes.
+constexpr int kCopyList = 48;
+struct CopyList {
+    struct Item {
+        void* dst;
+        const void* src;
+        uint64_t bytes;
+        uint32_t block0;   // first workgroup
+    } item[kCopyList];
+    int32_t n;
+    int32_t* clear;
+};
+void launch_copy_list(CopyList& L, hipStream_t s);
 // up to 8 arrays of n 8-byte values, one after another in dst
 struct PackList {
     const uint64_t* src[8];

@@ -1697,6 +1697,30 @@ template <typename T> struct Impl : ImplBase {
     Scratch snap;
     bool snap_valid = false;
 
+    // the blobs to (take) or from the snapshot, which lets them follow one another on
+    // 256-byte boundaries
+    flood_status copy_snapshot(const std::vector<Blob>& bl, bool take, std::string& err) {
+        CopyList L;
+        L.n = 0;
+        L.clear = take ? nullptr : status;
+        char* at = static_cast<char*>(snap.p);
+        for (size_t i = 0; i < bl.size(); ++i) {
+            if (bl[i].bytes) {
+                CopyList::Item& it = L.item[L.n++];
+                it.dst = take ? at : static_cast<char*>(bl[i].p);
+                it.src = take ? static_cast<char*>(bl[i].p) : at;
+                it.bytes = bl[i].bytes;
+            }
+            at += (bl[i].bytes + 255) / 256 * 256;
+            if (L.n == kCopyList || i + 1 == bl.size()) {
+                launch_copy_list(L, st);
+                L.n = 0;
+            }
+        }
+        HIPCHK(hipGetLastError());
+        return FLOOD_OK;
+    }
+
     flood_status device_snapshot(int op, std::string& err) override {
         if (op == FLOOD_SNAPSHOT_RELEASE) {
             HIPCHK(hipStreamSynchronize(st));
@@ -1722,21 +1746,12 @@ template <typename T> struct Impl : ImplBase {
                 }
                 snap.bytes = total;
             }
-            size_t off = 0;
-            for (const Blob& b : bl) {
-                HIPCHK(hipMemcpyAsync(static_cast<char*>(snap.p) + off, b.p, b.bytes, hipMemcpyDeviceToDevice, st));
-                off += (b.bytes + 255) / 256 * 256;
-            }
+            CHK(copy_snapshot(bl, true, err));
             snap_valid = true;
             return FLOOD_OK;
         }
         if (!snap_valid) { err = "no device snapshot has been taken"; return FLOOD_ESTATE; }
-        size_t off = 0;
-        for (const Blob& b : bl) {
-            HIPCHK(hipMemcpyAsync(b.p, static_cast<char*>(snap.p) + off, b.bytes, hipMemcpyDeviceToDevice, st));
-            off += (b.bytes + 255) / 256 * 256;
-        }
-        HIPCHK(hipMemsetAsync(status, 0, sizeof(int32_t), st));
+        CHK(copy_snapshot(bl, false, err));   // and clears the status word
         return FLOOD_OK;
     }
 
