@@ -128,6 +128,7 @@ template <> __device__ __forceinline__ double depth_add<double>(double h, double
 template <typename T, int V>
 __device__ __forceinline__ void depth_add_row(const T (&h)[V], const T (&inc)[V], uint32_t seed, uint32_t cell, T (&out)[V]) {
     if constexpr (sizeof(T) == 4) {
+        static_assert(V % 2 == 0, "whole pairs");
 #pragma unroll
         for (int j = 0; j < V; j += 2) {
             const uint32_t r = mix32(seed ^ ((cell >> 1) + (uint32_t)(j / 2)));
@@ -405,13 +406,16 @@ struct Rows {
         p = base;
         rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)bytes, 0x00020000);
     }
-    // V cells, 16 or 8 bytes together
+    // V cells, 16, 8 or 4 bytes together
     template <int V, bool NT>
     __device__ __forceinline__ void load(uint32_t vo, uint32_t so, T (&d)[V]) const {
         if constexpr (V * sizeof(T) == 16) {
             typedef unsigned int __attribute__((ext_vector_type(4))) u4;
             const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, (int)so, NT ? kBufNt : 0);
             __builtin_memcpy(d, &v, 16);
+        } else if constexpr (V * sizeof(T) == 4) {
+            const unsigned int v = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)vo, (int)so, NT ? kBufNt : 0);
+            __builtin_memcpy(d, &v, 4);
         } else {
             typedef unsigned int __attribute__((ext_vector_type(2))) u2;
             const u2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)vo, (int)so, NT ? kBufNt : 0);
@@ -430,6 +434,10 @@ struct Rows {
             u4 v;
             __builtin_memcpy(&v, d, 16);
             __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)vo, 0, NT ? kBufNt : 0);
+        } else if constexpr (V * sizeof(T) == 4) {
+            unsigned int v;
+            __builtin_memcpy(&v, d, 4);
+            __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)vo, 0, NT ? kBufNt : 0);
         } else {
             typedef unsigned int __attribute__((ext_vector_type(2))) u2;
             u2 v;

@@ -1291,6 +1291,14 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wg = xcd_order(blockIdx.x, gridDim.x, L.xcd_chunk) * (kBlock / 64) + wave;
+    // strips of one cell a lane: the depth maxima of a workgroup's wavefronts (see the end)
+    constexpr bool kCombine = V == 1 && REC != 1;
+    __shared__ HB wg_max[kCombine ? kBlock / 64 : 1];
+    __shared__ int wg_member[kCombine ? kBlock / 64 : 1];
+    if constexpr (kCombine) {
+        if (lane == 0) wg_member[wave] = -1;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // done before this wavefront can end
+    }
     int ci = 0;
     for (int i = 1; i < L.n_catch; ++i)
         if (wg >= L.c[i].wave_begin) ci = i;
@@ -1588,7 +1596,11 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
     }
 
     HB vmax = 0;
-    T vcl = T(0), vdr = T(0);
+    // Depth that clamping added, per lane.  In double where a step may also run in the
+    // tiled kernel, which adds cell by cell: the two then give one ledger.
+    using Clamped = std::conditional_t<RAG || V == 1, double, T>;
+    Clamped vcl = 0;
+    T vdr = T(0);
     double vdrain = 0.0;
     uint32_t cell = (uint32_t)r0 * (uint32_t)nx + (uint32_t)xl;
     // one row: m holds its loads, nxt takes those of the next row; odd: the second
@@ -1668,11 +1680,11 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
             if constexpr (lc) rn = ms.rinc * lut((ccw >> (8 * j)) & 0xffu, 4);
             inc[j] = ms.dtdx * dv + rn;
         }
-        if constexpr (RAG) {
+        if constexpr (RAG || V == 1) {
             // the first cell of the lane may be odd, so a pair's hash may serve two lanes
 #pragma unroll
             for (int j = 0; j < V; ++j) hn[j] = depth_add(hc[j], inc[j], ms.seed, cell + (uint32_t)j);
-            if (eastw) {
+            if (RAG && eastw) {
 #pragma unroll
                 for (int j = 0; j < V; ++j) hn[j] = j < tail ? hn[j] : T(0);
             }
@@ -1689,7 +1701,7 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
         if (__any(any)) {
 #pragma unroll
             for (int j = 0; j < V; ++j) {
-                vcl += neg[j] ? -hn[j] : T(0);
+                vcl += neg[j] ? (Clamped)-hn[j] : Clamped(0);
                 // the tape keeps a clamped depth as -0 (the clamp branch for the adjoint)
                 hn[j] = neg[j] ? (REC ? -T(0) : T(0)) : hn[j];
             }
@@ -1770,13 +1782,33 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
             if (lane == 0 && dr != 0.0)
                 atomicAdd(C.drain_acc + (size_t)k * kBins + (blockIdx.x & (kBins - 1)), dr * (C.dx * C.dx));
         }
-        vcl = own ? vcl : T(0);
-        if (__any(vcl != T(0))) {
+        vcl = own ? vcl : Clamped(0);
+        if (__any(vcl != Clamped(0))) {
             double cl = (double)vcl;
             for (int off = 32; off > 0; off >>= 1) cl += __shfl_xor(cl, off, 64);
             if (lane == 0) atomicAdd(&L.vclamp[mg], cl * (C.dx * C.dx));
         }
-        if (lane == 0 && vmax != 0) {
+        if constexpr (kCombine) {
+            // Small grids: what counts is the chain after the last row, and that atomics on
+            // the bins of few members meet on few cache lines (15 ns apiece), so the
+            // wavefronts of a member in a workgroup send one, without looking first.
+            // Wavefronts that had nothing to step have ended; the barrier is among the others.
+            if (lane == 0) {
+                wg_max[wave] = vmax;
+                wg_member[wave] = mg;
+            }
+            __syncthreads();
+            bool first = true;
+#pragma unroll
+            for (int w = 0; w < kBlock / 64; ++w) {
+                if (wg_member[w] != mg) continue;
+                first = first && w >= wave;
+                const HB o = wg_max[w];
+                vmax = o > vmax ? o : vmax;
+            }
+            if (first && lane == 0 && vmax != 0)
+                atomicMax((PLAN ? L.plan.bins_out : L.hbins) + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + mg, vmax);
+        } else if (lane == 0 && vmax != 0) {
             HB* bin = (PLAN ? L.plan.bins_out : L.hbins) + (size_t)(blockIdx.x & (kBins - 1)) * L.n_total + mg;
             const HB cur = __hip_atomic_load(bin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (vmax > cur) atomicMax(bin, vmax);
@@ -1790,6 +1822,12 @@ template <typename T, int EXT>
 static void launch_marchv_ext(const StepLaunch<T>& L, int nt, const dim3 grid, hipStream_t s) {
     constexpr int V = march_vec<T>();
     static_assert(sizeof(StepLaunch<T>) <= 4096, "kernel arguments");
+    if constexpr (EXT == 0 || EXT == kMarchPeak)
+        if (L.narrow) {
+            if (L.plan.pc) hipLaunchKernelGGL((k_marchv<T, 1, 0, 0, EXT, true>), grid, dim3(kBlock), 0, s, L);
+            else hipLaunchKernelGGL((k_marchv<T, 1, 0, 0, EXT, false>), grid, dim3(kBlock), 0, s, L);
+            return;
+        }
     if (L.plan.pc && nt)
         hipLaunchKernelGGL((k_marchv<T, V, 1, 0, EXT, true>), grid, dim3(kBlock), 0, s, L);
     else if (L.plan.pc)
@@ -1824,17 +1862,22 @@ void launch_marchv(const StepLaunch<T>& L, int nt, int ext, int total_waves, hip
 // the launch are skipped.  Recording forward (record = 1): the same blocks and
 // marks, plus everything the plain step
 // updates (depth maximum bins, clamp and outflow ledgers, running maximum).
-template <typename T>
-void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s) {
+template <typename T, int V, int NT>
+static void launch_marchv_rec_v(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s) {
     const int per = kBlock / 64;
     const dim3 grid((total_waves + per - 1) / per);
-    constexpr int V = march_vec<T>();
     if (record && L.c[0].peak)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, kMarchPeak, false>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, NT, 2, kMarchPeak, false>), grid, dim3(kBlock), 0, s, L);
     else if (record)
-        hipLaunchKernelGGL((k_marchv<T, V, 1, 2, 0, false>), grid, dim3(kBlock), 0, s, L);
+        hipLaunchKernelGGL((k_marchv<T, V, NT, 2, 0, false>), grid, dim3(kBlock), 0, s, L);
     else
         hipLaunchKernelGGL((k_marchv<T, V, 0, 1, 0, false>), grid, dim3(kBlock), 0, s, L);
+}
+
+template <typename T>
+void launch_marchv_rec(const StepLaunch<T>& L, int record, int total_waves, hipStream_t s) {
+    if (L.narrow) launch_marchv_rec_v<T, 1, 0>(L, record, total_waves, s);
+    else launch_marchv_rec_v<T, march_vec<T>(), 1>(L, record, total_waves, s);
 }
 
 template void launch_marchv<float>(const StepLaunch<float>&, int, int, int, hipStream_t);

@@ -70,6 +70,7 @@ template <typename T> struct Impl : ImplBase {
     int variant = 1;          // 1 tiled step kernel, 2 row-marching step kernel (mi == 1)
     int march_seg = 2;        // members per wavefront of the row-marching kernel
     int march_order = 1;      // wavefront order of the row-marching kernel
+    int march_narrow = -1;    // strips of one cell a lane in the vectorised row march: as measured, -1 by rule
     int forced_order = -1;    // >= 0: the only order the tuner tries
     int march_bands = 0;      // order 4: bands of rows of strips (multiple of 8); 0: from the L2 size
     int march_nt = 1;         // non-temporal state streams in the vectorised row-marching kernel
@@ -327,11 +328,38 @@ template <typename T> struct Impl : ImplBase {
         return l;
     }
 
+    // Wavefronts that a step over the members of a catchment takes in strips of whole
+    // vectors, two rows tall, and whether strips of one cell a lane are the better ones:
+    // where those do not fill the chip's 1024 SIMDs, the four times (FP64: twice) as many
+    // wavefronts are shorter chains of arithmetic, and in FP32 no lanes idle beside a
+    // narrow grid.  A step in FP32: 97 x 83 x 5 7.2 us from 10.5, 128 x 128 x 4 7.2 from 9.1, 512 x
+    // 512 x 2 9.9 from 12.5, 256 x 256 x 16 13.4 from 12.7; in FP64 128 x 128 x 4 7.6 from 9.4,
+    // 256 x 256 x 4 10.2 from 10.2.  By rule where nothing is measured; else both compete.
+    static size_t wide_pairs(int ny, int nx, int members) {
+        const int w = 64 * march_vec<T>();
+        return (size_t)((nx + w - 1) / w) * ((ny + 1) / 2) * members;
+    }
+    static bool narrow_pays(size_t pairs) { return pairs < (sizeof(T) == 4 ? 1024 : 512); }
+    bool narrow_ok() const { return mi == 1 && !any_land && !any_inflow; }
+    // FP32 ensembles of up to 2^20 member cells: always in narrow strips, and adjoints of
+    // handles that name no kernel in the tiled form, whose single-precision sums over
+    // tiles are the rain-multiplier gradients that such ensembles have always had
+    bool small_fp32() const {
+        size_t cells = 0;
+        for (const Cat& c : cats) cells += (size_t)c.ny * c.nx * c.N;
+        return sizeof(T) == 4 && cells <= (size_t)1 << 20;
+    }
+    bool adj_tiled = false;   // adjoints in the tiled form although the steps march (see small_fp32)
+
     // tile / grouping geometry of every catchment and the launch descriptor
     void layout_launch() {
         int begin = 0, waves = 0;
         SL.n_catch = n_catch;
         SL.n_total = n_total;
+        size_t pairs = 0;
+        for (const Cat& c : cats) pairs += wide_pairs(c.ny, c.nx, c.N);
+        SL.narrow = variant == 3 && narrow_ok() &&
+                    (small_fp32() || (march_narrow >= 0 ? march_narrow != 0 : narrow_pays(pairs)));
         for (int i = 0; i < n_catch; ++i) {
             Cat& c = cats[i];
             CatchDev<T>& d = c.dev;
@@ -346,7 +374,7 @@ template <typename T> struct Impl : ImplBase {
             d.block_begin = begin;
             begin += d.n_blocks;
             d.march_rows = std::max(1, std::min(c.march_rows, c.ny));
-            const int strip_w = variant == 3 ? 64 * march_vec<T>() : 62;
+            const int strip_w = variant != 3 ? 62 : SL.narrow ? 64 : 64 * march_vec<T>();
             d.strips_x = (c.nx + strip_w - 1) / strip_w;
             d.strips_xa = (c.nx + 62 * adj_vec<T>() - 1) / (62 * adj_vec<T>());
             d.strips_y = (c.ny + d.march_rows - 1) / d.march_rows;
@@ -389,7 +417,8 @@ template <typename T> struct Impl : ImplBase {
     void launch_steps(const StepLaunch<T>& L) {
         if (variant == 3 && !L.recompute)
             launch_marchv<T>(L, march_nt,
-                             (any_land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() ? 0 : 4) | (L.c[0].peak ? 8 : 0),
+                             (any_land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() || L.narrow ? 0 : 4) |
+                                 (L.c[0].peak ? 8 : 0),
                              total_waves, st);
         else if (variant == 2 && !L.recompute)
             launch_march<T>(L, march_seg, total_waves, st);
@@ -850,11 +879,13 @@ template <typename T> struct Impl : ImplBase {
     // without advancing it: each trial launches one step kernel that reads the
     // current copy and writes the other copy, which is dead until the next step.
     flood_status autotune_geometry(const TuneKey& key, const flood_params* params, std::string& err) {
+        adj_tiled = params[0].step_kernel == 0 && narrow_ok() && small_fp32();
         TuneChoice cached;
         if (tune_lookup(key, mi, cached)) {
             if (!params[0].step_kernel && mi == 1 && !vector_only()) variant = cached.variant;
             if (!params[0].march_members) march_seg = cached.march_seg;
             march_order = forced_order >= 0 ? forced_order : cached.march_order;
+            march_narrow = cached.march_narrow;
             for (int i = 0; i < n_catch; ++i) {
                 if (!params[i].tile_rows) cats[i].tile_rows = cached.tile_rows;
                 if (!params[i].chunks_per_block) cats[i].cpb = cached.cpb;
@@ -919,19 +950,15 @@ template <typename T> struct Impl : ImplBase {
         for (int v = 1; v < max_chunks; v *= 2) cpbs.push_back(v);
         cpbs.push_back(max_chunks);
         struct Cand {
-            int variant, rows, cpb, mrows, seg, order;
+            int variant, rows, cpb, mrows, seg, order, narrow = 0;
         };
         std::vector<Cand> cands;
         // Left to itself the library steps members in planes with the vectorised row
-        // march, of any row length.  The tiled kernel serves interleaved members and
-        // competes where a launch holds few cells: it reads a cell's neighbours at once
-        // where the march goes row by row (128 x 128 cells in FP64: 8.4 us against 12;
-        // from about 130,000 cells on the march was the faster one in every trial).  The
-        // scalar march serves whoever asks for it by number.
-        size_t cells = 0;
-        for (const Cat& c : cats) cells += (size_t)c.ny * c.nx * c.N;
-        const bool want1 = !vector_only() && (params[0].step_kernel == 1 || mi != 1 ||
-                                              (params[0].step_kernel == 0 && cells <= (size_t)1 << 17));
+        // march, of any row length: no other kernel was faster at any size, on the
+        // smallest grids 7 us a step against 8.4 and a planner launch for the tiled one.
+        // That serves interleaved members, and it and the scalar march whoever asks for
+        // them by number.
+        const bool want1 = !vector_only() && (params[0].step_kernel == 1 || mi != 1);
         const bool want2 = !vector_only() && mi == 1 && params[0].step_kernel == 2;
         const bool want3 = mi == 1 && (params[0].step_kernel == 0 || params[0].step_kernel == 3);
         if (want1)
@@ -956,8 +983,15 @@ template <typename T> struct Impl : ImplBase {
             // that the drained volume is summed by
             const std::vector<int> heights = any_land ? std::vector<int>{8, 16, 32, 64} : std::vector<int>{2, 4, 8, 16, 32, 64};
             for (int od : {0, 1, 2, 3, 4})
-                if (forced_order < 0 || od == forced_order)
-                    for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od});
+                if ((forced_order < 0 || od == forced_order) && !(narrow_ok() && small_fp32()))
+                    for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 0});
+            // strips of one cell a lane compete while the chip holds all the others' wavefronts
+            size_t pairs = 0;
+            for (const Cat& c : cats) pairs += wide_pairs(c.ny, c.nx, c.N);
+            if (narrow_ok() && pairs <= 8192)
+                for (int od : {0, 1, 2, 3, 4})
+                    if (forced_order < 0 || od == forced_order)
+                        for (int mr : {1, 2, 4, 8, 16}) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 1});
         }
         Cand bc = cands.empty()
                       ? Cand{variant, cats[0].tile_rows, cats[0].cpb, cats[0].march_rows, march_seg, march_order}
@@ -969,6 +1003,7 @@ template <typename T> struct Impl : ImplBase {
             variant = cd.variant;
             march_seg = cd.seg;
             march_order = cd.order;
+            march_narrow = cd.narrow;
             for (int i = 0; i < n_catch; ++i) {
                 if (!params[i].tile_rows) cats[i].tile_rows = cd.rows;
                 if (!params[i].chunks_per_block) cats[i].cpb = cd.cpb;
@@ -1019,7 +1054,7 @@ template <typename T> struct Impl : ImplBase {
             float pick_t = 1e30f;
             for (const auto& r : round2) {
                 const Cand& cd = cands[r.second];
-                if (cd.variant == bc.variant && cd.order == 4 && cd.seg == bc.seg && r.first <= 1.01f * best_all &&
+                if (cd.variant == bc.variant && cd.narrow == bc.narrow && cd.order == 4 && cd.seg == bc.seg && r.first <= 1.01f * best_all &&
                     r.first < pick_t) {
                     pick = (int)r.second;
                     pick_t = r.first;
@@ -1035,12 +1070,13 @@ template <typename T> struct Impl : ImplBase {
         for (const auto& r : round2) {
             const Cand& cd = cands[r.second];
             if (r.first <= 1.01f * best && cd.variant == bc.variant && cd.order == bc.order && cd.variant >= 2 &&
-                cd.seg == bc.seg && cd.mrows > bc.mrows)
+                cd.narrow == bc.narrow && cd.seg == bc.seg && cd.mrows > bc.mrows)
                 bc = cd;
         }
         variant = bc.variant;
         march_seg = bc.seg;
         march_order = bc.order;
+        march_narrow = bc.narrow;
         for (int i = 0; i < n_catch; ++i) {
             if (!params[i].tile_rows) cats[i].tile_rows = bc.rows;
             if (!params[i].chunks_per_block) cats[i].cpb = bc.cpb;
@@ -1114,6 +1150,7 @@ template <typename T> struct Impl : ImplBase {
         c.march_rows = bc.mrows;
         c.march_seg = bc.seg;
         c.march_order = bc.order;
+        c.march_narrow = bc.narrow;
         for (int i = 0; i < n_catch && i < 8; ++i) c.march_rows_c[i] = cats[i].march_rows;
         // only a search over the full candidate set is remembered: a handle that
         // pinned part of the geometry measured a subset, whose best need not be
@@ -2014,7 +2051,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
     // members in planes with a vectorisable row length: the adjoint runs in
     // row-march form (forward, tape recomputation and reverse step), otherwise
     // in the tiled form that also serves interleaved members
-    const bool march_adj = variant == 3 && vector_ok();
+    const bool march_adj = variant == 3 && vector_ok() && !adj_tiled;
     size_t env_group = 0;
     if (const char* eg = std::getenv("FLOOD_ADJ_GROUP")) {   // testing: force smaller member groups
         const long v = std::atol(eg);
@@ -2335,9 +2372,10 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
         StepLaunch<T> SLg = SL;
         SLg.n_catch = 1;
         SLg.c[0] = V;
-        SLg.c[0].groups = (V.n_chunks + std::max(1, std::min(C.cpb, V.n_chunks)) - 1) /
-                          std::max(1, std::min(C.cpb, V.n_chunks));
-        SLg.c[0].chunks_per_group = std::max(1, std::min(C.cpb, V.n_chunks));
+        // chunks per workgroup: as tuned for the tiled kernel, one where the steps march
+        const int cpb = variant == 3 ? 1 : std::max(1, std::min(C.cpb, V.n_chunks));
+        SLg.c[0].groups = (V.n_chunks + cpb - 1) / cpb;
+        SLg.c[0].chunks_per_group = cpb;
         SLg.c[0].n_blocks = V.tiles_x * V.tiles_y * SLg.c[0].groups;
         SLg.total_blocks = SLg.c[0].n_blocks;
         SLg.recompute = 0;
@@ -2370,9 +2408,12 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             CatchDev<T> TVF = TV;
             TVF.out_acc = V.out_acc;
             TVF.peak = V.peak;
+            const bool narrow = narrow_pays(wide_pairs(C.ny, C.nx, Gg));
+            if (narrow) TVF.strips_x = (C.nx + 63) / 64;
             set_march_rows(TVF, adj_rows(kAdjMarchRows, TVF.strips_x * Gg, C.ny, 4), Gg);
             if (const char* fr = std::getenv("FLOOD_ADJ_FROWS")) set_march_rows(TVF, std::max(1, std::atoi(fr)), Gg);
             CatchDev<T> TVR = TV;   // tape recomputation: the forward's geometry
+            TVR.strips_x = TVF.strips_x;
             TVR.march_rows = TVF.march_rows;
             TVR.strips_y = TVF.strips_y;
             TVR.march_bands = TVF.march_bands;
@@ -2403,6 +2444,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             SLm.c[0] = V;
             SLm.total_blocks = 0;
             SLm.recompute = 0;
+            SLm.narrow = narrow;
             // launches per batch: a member takes at most one step per launch, so a
             // batch never takes a member past the segment's ckpt_every steps
             const int B = Bm;

@@ -4,7 +4,8 @@
 // one problem shape after the first do not measure again, and optionally in a
 // file: $FLOOD_TUNE_CACHE, one line per tuned problem,
 // "<key> mi tile_rows cpb variant march_rows march_seg march_order rows_1,...,rows_n"
-// (the last field: each catchment's rows per strip, 0 for march_rows).  Set
+// and, since strips of one cell a lane compete, " march_narrow"
+// (rows_i: each catchment's rows per strip, 0 for march_rows).  Set
 // FLOOD_AUTOTUNE=0 to skip measuring and use the defaults (or the explicit
 // values given at creation).
 #include "flood_tune.h"
@@ -65,17 +66,18 @@ bool tune_lookup(const TuneKey& k, int mi, TuneChoice& out) {
     if (!f) return false;
     const std::string want = key_string(k, mi);
     char line[1024], key[512], rows[256];
-    int a, b, c, d, e, f2, g2;
+    int a, b, c, d, e, f2, g2, nar;
     bool found = false;
     while (std::fgets(line, sizeof line, f)) {
         rows[0] = 0;
-        const int got = std::sscanf(line, "%511s %d %d %d %d %d %d %d %255s", key, &a, &b, &c, &d, &e, &f2, &g2, rows);
+        const int got = std::sscanf(line, "%511s %d %d %d %d %d %d %d %255s %d", key, &a, &b, &c, &d, &e, &f2, &g2, rows, &nar);
         if (got < 8) continue;
+        if (got < 10) nar = -1;
         // an entry outside the geometries this library launches is ignored
         bool sane = (a == 1 || a == 2 || a == 4 || a == 8) && b >= 1 && b <= 8 && c >= 1 && d >= 1 && d <= 3 &&
-                    e >= 1 && e <= 4096 && (f2 == 1 || f2 == 2 || f2 == 4 || f2 == 8) && g2 >= 0 && g2 <= 4;
+                    e >= 1 && e <= 4096 && (f2 == 1 || f2 == 2 || f2 == 4 || f2 == 8) && g2 >= 0 && g2 <= 4 && nar >= -1 && nar <= 1;
         int rc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (got == 9) {
+        if (got >= 9) {
             const char* p = rows;
             for (int i = 0; i < k.n_catch && i < 8 && *p; ++i) {
                 char* end = nullptr;
@@ -93,6 +95,7 @@ bool tune_lookup(const TuneKey& k, int mi, TuneChoice& out) {
             out.march_rows = e;
             out.march_seg = f2;
             out.march_order = g2;
+            out.march_narrow = nar;
             for (int i = 0; i < 8; ++i) out.march_rows_c[i] = rc[i];
             found = true;
         }
@@ -112,8 +115,8 @@ void tune_store(const TuneKey& k, const TuneChoice& c) {
     if (!f) return;
     std::string rows;
     for (int i = 0; i < k.n_catch && i < 8; ++i) rows += (i ? "," : "") + std::to_string(c.march_rows_c[i]);
-    std::fprintf(f, "%s %d %d %d %d %d %d %d %s\n", key_string(k, c.mi).c_str(), c.mi, c.tile_rows, c.cpb, c.variant,
-                 c.march_rows, c.march_seg, c.march_order, rows.c_str());
+    std::fprintf(f, "%s %d %d %d %d %d %d %d %s %d\n", key_string(k, c.mi).c_str(), c.mi, c.tile_rows, c.cpb, c.variant,
+                 c.march_rows, c.march_seg, c.march_order, rows.c_str(), c.march_narrow);
     std::fclose(f);
 }
 

@@ -19,6 +19,7 @@ struct TuneChoice {
     int march_rows = 32; // rows per strip of the row-marching kernel
     int march_seg = 2;   // members marched together by one wavefront
     int march_order = 1; // wavefront order of the row-march kernels (0 to 4)
+    int march_narrow = -1; // vectorised row march: 1 strips of one cell a lane, 0 of whole vectors, -1 by rule
     int march_rows_c[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // per catchment, 0: march_rows
 };
 

@@ -115,3 +115,28 @@ def test_steps_that_plan_themselves(fl, monkeypatch, rb):
         got = run(batch)
         for a, b in zip(ref, got):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+@pytest.mark.parametrize("ny,nx,rows", [(1, 1, 1), (5, 63, 1), (6, 64, 2), (7, 65, 3), (131, 129, 8), (66, 200, 64)])
+def test_strips_of_one_cell_a_lane(fl, monkeypatch, rb, ny, nx, rows):
+    # few wavefronts: strips of 64 cells, whose maxima a workgroup sends together
+    monkeypatch.setenv("FLOOD_AUTOTUNE", "0")
+    _same(fl, _catch(ny, nx, 3), 20.0, real_bytes=rb, march_rows=rows)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+@pytest.mark.parametrize("ny,nx,members,rows", [(5, 1, 400, 2), (70, 255, 30, 7), (66, 259, 20, 64)])
+def test_ragged_rows_of_many_members(fl, monkeypatch, rb, ny, nx, members, rows):
+    # enough wavefronts: strips of whole vectors, the last of a row cut short
+    monkeypatch.setenv("FLOOD_AUTOTUNE", "0")
+    _same(fl, _catch(ny, nx, members), 10.0, real_bytes=rb, march_rows=rows)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+def test_members_that_end_at_different_times_in_narrow_strips(fl, monkeypatch, rb):
+    # wavefronts of members past their end leave workgroups whose others go on
+    monkeypatch.setenv("FLOOD_AUTOTUNE", "0")
+    cat = _catch(9, 130, 6)
+    cat["rain_mult"] = np.array([0.0, 40.0, 0.1, 20.0, 5.0, 1.0])
+    _same(fl, cat, 60.0, real_bytes=rb, march_rows=2)
