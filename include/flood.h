@@ -218,7 +218,8 @@ flood_status flood_assimilate(flood_handle* h, int32_t catchment, int32_t n_gaug
  * device memory.  The forward run of a group records every step of every
  * member, its length and its state, in a tape: the row-march form (members in
  * planes with whole vectors of cells in every row, step kernel 3; FP32 handles
- * of up to 2^20 member cells that leave the kernel open take the tiled form) keeps one state per member step in a pool of blocks
+ * that leave the kernel open take the tiled form up to 2^20 member cells, and
+ * beyond where strips of 256 cells would leave many lanes idle) keeps one state per member step in a pool of blocks
  * shared by the group, the tiled form ckpt_every + 1 states per member.  A
  * segment ends when a member has taken ckpt_every steps in it (or the pool
  * could run out), or, in the row-march form, earlier where that lets the steps

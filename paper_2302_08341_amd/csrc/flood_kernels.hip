@@ -578,8 +578,8 @@ void launch_hmax_init(int mi, const CatchDev<T>& C, const int32_t* par, typename
 // Bound by the read of the depths.  A few workgroups per member, each over many
 // cells: their sums meet in atomics on one or two cache lines, about 20 ns apiece,
 // and with one workgroup per 256 cells those were the whole time (1024 x 1024 x 16:
-// 320 us then, 46 now; 2000 x 2000 x 96: 725, 257, 6.0 TB/s).  Four independent partial sums per thread; cells of a member lie
-// `mi` apart.
+// 320 us then, 46 now; 2000 x 2000 x 96: 725, 257, 6.0 TB/s).  Independent partial
+// sums for the cells of a vector; cells of a member lie `mi` apart.
 template <typename T, int V>
 __global__ __launch_bounds__(256) void k_storage(const CatchDev<T> C, int mi, const int32_t* par, double* out) {
     const int m = blockIdx.y;
@@ -1278,6 +1278,10 @@ __device__ __forceinline__ bool plan_step(const StepPlan<T>& P, const PlanCatch&
 }
 
 // PLAN: the step is planned here (REC = 0), else by k_plan into L.ms.
+// V: cells per lane, 16 bytes of them, or one.  With one a strip is 64 cells wide: small
+// grids, bound by the chain of a wavefront's arithmetic (0.35 us a row against 1.3 us)
+// and by lanes that idle beside a row shorter than 256 cells, get more and shorter ones
+// (97 x 83 x 5 in FP32 7.2 us a step from 10.5; see narrow_pays for where the line lies).
 // Wavefronts per SIMD the registers are budgeted for: four in FP32 (128 registers; three
 // where inflow links meet another extension and four would spill), two in FP64.
 template <typename T> constexpr int march_occupancy(int ext) {

@@ -341,15 +341,34 @@ template <typename T> struct Impl : ImplBase {
     }
     static bool narrow_pays(size_t pairs) { return pairs < (sizeof(T) == 4 ? 1024 : 512); }
     bool narrow_ok() const { return mi == 1 && !any_land && !any_inflow; }
-    // FP32 ensembles of up to 2^20 member cells: always in narrow strips, and adjoints of
-    // handles that name no kernel in the tiled form, whose single-precision sums over
-    // tiles are the rain-multiplier gradients that such ensembles have always had
+    // FP32 ensembles of up to 2^20 member cells: always in narrow strips
     bool small_fp32() const {
         size_t cells = 0;
         for (const Cat& c : cats) cells += (size_t)c.ny * c.nx * c.N;
         return sizeof(T) == 4 && cells <= (size_t)1 << 20;
     }
-    bool adj_tiled = false;   // adjoints in the tiled form although the steps march (see small_fp32)
+    bool adj_tiled = false;   // adjoints in the tiled form although the steps march
+    // The rain-multiplier gradients of the two adjoint forms differ by some 1e-7 in FP32:
+    // the tiled one sums tiles in single precision, the row march in double.  Handles
+    // that name no kernel keep the form, and so the sums, of the step kernel that was
+    // measured the fastest before ragged rows and narrow strips could march: the tiled one
+    // up to 2^20 member cells, then the scalar march (tiled adjoints too) where strips of 256
+    // cells leave more lanes idle than its strips of 62.  Of 190 shapes of 9,000 to 6 million
+    // member cells timed, 185 fall on the side that the trial took.
+    bool tiled_adjoint_by_shape() const {
+        if (sizeof(T) != 4 || !narrow_ok()) return false;
+        if (small_fp32()) return true;
+        double wide = 0.0, slim = 0.0, cells = 0.0;
+        bool long_rows = true;
+        for (const Cat& c : cats) {
+            const double rows = (double)c.ny * c.N;
+            wide += rows * (256 * ((c.nx + 255) / 256));
+            slim += rows * (62 * ((c.nx + 61) / 62));
+            cells += rows * c.nx;
+            long_rows = long_rows && c.nx > 256;
+        }
+        return wide > slim * (cells < 2.6e6 && long_rows ? 1.4 : cells < 4.2e6 ? 1.04 : 1.02);
+    }
 
     // tile / grouping geometry of every catchment and the launch descriptor
     void layout_launch() {
@@ -879,7 +898,7 @@ template <typename T> struct Impl : ImplBase {
     // without advancing it: each trial launches one step kernel that reads the
     // current copy and writes the other copy, which is dead until the next step.
     flood_status autotune_geometry(const TuneKey& key, const flood_params* params, std::string& err) {
-        adj_tiled = params[0].step_kernel == 0 && narrow_ok() && small_fp32();
+        adj_tiled = params[0].step_kernel == 0 && tiled_adjoint_by_shape();
         TuneChoice cached;
         if (tune_lookup(key, mi, cached)) {
             if (!params[0].step_kernel && mi == 1 && !vector_only()) variant = cached.variant;
