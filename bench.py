@@ -622,7 +622,7 @@ def main():
                 "avg_launch_ms": round(avg_ms, 4), "launches": launches,
                 "timing": "a HIP event pair around every captured batch of %d step launches in the timed region "
                           "(the graph path that value is measured on); a step launch's time holds the step kernel, "
-                          "its planner kernel and the gaps between them" % conf_end["graph_steps"],
+                          "which plans its own step, and the gaps between launches" % conf_end["graph_steps"],
                 "algorithmic_bytes_per_launch": round(alg_bytes),
                 "traffic_over_algorithmic": round(traffic / alg_bytes, 3) if traffic else None,
                 "kernel_sources_sha256": kernel_source_hash()}
