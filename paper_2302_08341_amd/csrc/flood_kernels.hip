@@ -1712,9 +1712,9 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
         }
         if constexpr (lc) {
             // drainage of draining classes, up to the water the cell holds; summed per
-            // eight rows of the grid, so that the sum is the same for every strip height
-            // that is a multiple of eight
-            if ((r & 7) == 0) {
+            // drain_rows rows of the grid, so that the sum is the same for every strip
+            // height that is a multiple of them
+            if ((r & (L.drain_rows - 1)) == 0) {
                 vdrain += (double)vdr;
                 vdr = T(0);
             }

@@ -370,11 +370,19 @@ template <typename T> struct Impl : ImplBase {
         return wide > slim * (cells < 2.6e6 && long_rows ? 1.4 : cells < 4.2e6 ? 1.04 : 1.02);
     }
 
+    static constexpr double kDrainCells = 4.5e6;
+
     // tile / grouping geometry of every catchment and the launch descriptor
     void layout_launch() {
         int begin = 0, waves = 0;
         SL.n_catch = n_catch;
         SL.n_total = n_total;
+        // the drained volume's single-precision partial sums are those of the strip height
+        // that land cover has been measured the fastest at: 4 rows up to 4.5 million member
+        // cells (27 shapes of 27), mostly 8 beyond
+        double all_cells = 0.0;
+        for (const Cat& c : cats) all_cells += (double)c.ny * c.nx * c.N;
+        SL.drain_rows = all_cells <= kDrainCells ? 4 : 8;
         size_t pairs = 0;
         for (const Cat& c : cats) pairs += wide_pairs(c.ny, c.nx, c.N);
         SL.narrow = variant == 3 && narrow_ok() &&
@@ -998,9 +1006,10 @@ template <typename T> struct Impl : ImplBase {
         }
         if (want3) {
             // strips of 2 rows pay where a launch has too few wavefronts for the chip
-            // otherwise; with land cover heights are multiples of eight rows, the blocks
-            // that the drained volume is summed by
-            const std::vector<int> heights = any_land ? std::vector<int>{8, 16, 32, 64} : std::vector<int>{2, 4, 8, 16, 32, 64};
+            // otherwise; with land cover heights are multiples of the rows that the drained
+            // volume is summed by
+            std::vector<int> heights = {2, 4, 8, 16, 32, 64};
+            if (any_land) heights.erase(heights.begin(), heights.begin() + (SL.drain_rows == 4 ? 1 : 2));
             for (int od : {0, 1, 2, 3, 4})
                 if ((forced_order < 0 || od == forced_order) && !(narrow_ok() && small_fp32()))
                     for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 0});
