@@ -66,7 +66,7 @@ KERNEL_NAMES = {1: "k_step", 2: "k_march", 3: "k_marchv"}
 KERNEL_TITLES = {1: "k_step (tiled fused step)", 2: "k_march (row-march fused step)",
                  3: "k_marchv (vectorised row-march fused step)"}
 KERNEL_SOURCES = ("paper_2302_08341_amd/csrc/flood_kernels.hip", "paper_2302_08341_amd/csrc/flood_device.h",
-                  "paper_2302_08341_amd/csrc/flood_internal.h")
+                  "paper_2302_08341_amd/csrc/flood_internal.h", "paper_2302_08341_amd/csrc/flood_rows.h")
 
 
 def log(msg):

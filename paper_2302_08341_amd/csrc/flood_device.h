@@ -4,6 +4,7 @@
 #pragma once
 
 #include "flood_internal.h"
+#include "flood_rows.h"
 
 namespace flood {
 
@@ -394,8 +395,8 @@ __device__ __forceinline__ void vstore_nt(T* p, const T (&d)[V]) {
 // A row array of the march behind a buffer descriptor (four scalar registers).
 // Load addresses are a lane's byte offset vo plus a wavefront-uniform byte offset
 // so; an access past the array's end reads zero or is dropped, so kPastEnd as vo
-// switches a lane off.  The base must be wavefront-uniform.
-constexpr uint32_t kPastEnd = 0xc0000000u;   // arrays are at most 2^31 bytes
+// switches a lane off.  The base must be wavefront-uniform.  A scalar offset is always
+// that of a row of the array; an offset that may lie past it goes into vo.
 constexpr int kBufNt = 2;                    // cache policy: non-temporal
 
 template <typename T>

@@ -214,6 +214,9 @@ template <typename T, int MI> void launch_step(const StepLaunch<T>& L, hipStream
 template <typename T> void launch_step_mi(int mi, const StepLaunch<T>& L, hipStream_t s);
 template <typename T> void launch_march(const StepLaunch<T>& L, int seg, int total_waves, hipStream_t s);
 // cells per lane of the vectorised row-marching kernel (nx must be a multiple of it)
+// elements that an array of rows is allocated beyond its last one: a lane of the row
+// march loads a whole vector of cells, up to three of them past the end of its row
+constexpr size_t kRowPad = 4;
 template <typename T> constexpr int march_vec() { return sizeof(T) == 4 ? 4 : 2; }
 // Cells per lane of the adjoint's reverse row march, in both precisions: with
 // four FP32 cells per lane the reverse step needs 138 VGPRs (3 waves per SIMD),

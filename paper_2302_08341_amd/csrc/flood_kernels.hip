@@ -1083,7 +1083,7 @@ __global__ __launch_bounds__(kBlock) void k_march(const StepLaunch<T> L) {
 // multiple of 64 V cells, so with a row pitch that is a multiple of 16 cells its
 // stores cover whole 64-byte blocks and no block is shared with a neighbouring
 // strip.  Where nx is no multiple of V (EXT bit 2) the last lane of a row owns
-// the remainder: it loads V cells all the same (the arrays are padded by V
+// the remainder: it loads V cells all the same (the arrays are padded by kRowPad
 // elements) and stores its own one by one.
 //
 // What bounds it is vector issue as much as HBM, so the row loop holds nothing
@@ -1437,22 +1437,22 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
     T bW = T(0), bN = T(0), bE = T(0), bH = T(0), bZ = T(0);
     const int cw = westw ? 0 : x0 - 1, ce = eastw ? nx - 1 : x0 + 64 * V;
     const bool wl = lane < 2, el = lane > 61;
-    const uint32_t hat = wl ? (uint32_t)lane * (uint32_t)nx + (uint32_t)cw
-                            : (uint32_t)(63 - lane) * (uint32_t)nx + (uint32_t)ce;   // cell, from row r
-    const uint32_t hv = (wl || el) ? hat * es : kPastEnd;
+    const uint32_t hat = beside_cell(lane, (uint32_t)nx, (uint32_t)cw, (uint32_t)ce);   // from row r
+    const uint32_t hv = beside_lane(lane) ? hat * es : kPastEnd;
     const uint32_t qv = wl ? (westw ? (uint32_t)lane * es : hv) : kPastEnd;
     const uint32_t qev = (el && eastw) ? hv : kPastEnd;
     Rows<T> QH;
     QH.set(westw ? QWs : QX.p, westw ? (uint32_t)ny * es : bytes);
     auto beside_load = [&](int r, uint32_t so) {
-        hx.h = H.load1(hv, so);
-        hx.z = Z.load1(hv, so);
-        hx.q = QH.load1(qv, westw ? (uint32_t)r * es : so);
-        hx.qe = QX.load1(qev, so);
+        const uint32_t at = beside_at(hv, so);
+        hx.h = H.load1(at, 0);
+        hx.z = Z.load1(at, 0);
+        hx.q = QH.load1(beside_at(qv, westw ? (uint32_t)r * es : so), 0);
+        hx.qe = QX.load1(beside_at(qev, so), 0);
         if constexpr (lc)
-            hx.cls = CLS.load8((wl || el) ? hat : kPastEnd, so / es);
+            hx.cls = CLS.load8(beside_at(beside_lane(lane) ? hat : kPastEnd, so / es), 0);
         else
-            hx.n = NM.load1(hv, so);
+            hx.n = NM.load1(at, 0);
     };
     // h0, z0, n0: the lane's first cell in row r, h1, z1, n1: in row r + 1
     auto beside = [&](T h0, T z0, T n0, T h1, T z1, T n1) {

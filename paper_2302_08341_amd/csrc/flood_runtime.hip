@@ -640,11 +640,11 @@ template <typename T> struct Impl : ImplBase {
                 d.edge_slope[e] = (T)c.edge_slope[e];
             }
             for (int k = 0; k < 2; ++k) {
-                CHK(dalloc(&d.h[k], c.state_elems, err));
-                CHK(dalloc(&d.qx[k], c.state_elems, err));
-                CHK(dalloc(&d.qy[k], c.state_elems, err));
-                CHK(dalloc(&d.qw[k], c.strip_w, err));
-                CHK(dalloc(&d.qn[k], c.strip_n, err));
+                CHK(dalloc(&d.h[k], c.state_elems + kRowPad, err));
+                CHK(dalloc(&d.qx[k], c.state_elems + kRowPad, err));
+                CHK(dalloc(&d.qy[k], c.state_elems + kRowPad, err));
+                CHK(dalloc(&d.qw[k], c.strip_w + kRowPad, err));
+                CHK(dalloc(&d.qn[k], c.strip_n + kRowPad, err));
                 HIPCHK(hipMemsetAsync(d.h[k], 0, c.state_elems * sizeof(T), st));
                 HIPCHK(hipMemsetAsync(d.qx[k], 0, c.state_elems * sizeof(T), st));
                 HIPCHK(hipMemsetAsync(d.qy[k], 0, c.state_elems * sizeof(T), st));
@@ -653,8 +653,8 @@ template <typename T> struct Impl : ImplBase {
             }
             T* zz;
             T* nn;
-            CHK(dalloc(&zz, ncell, err));
-            CHK(dalloc(&nn, ncell, err));
+            CHK(dalloc(&zz, ncell + kRowPad, err));
+            CHK(dalloc(&nn, ncell + kRowPad, err));
             {
                 std::vector<T> hz(ncell), hn(ncell);
                 for (size_t j = 0; j < ncell; ++j) {
@@ -713,7 +713,7 @@ template <typename T> struct Impl : ImplBase {
                 if (nq) HIPCHK(hipMemcpy(c.d_inflow_q, params[i].inflow_q, nq * sizeof(double), hipMemcpyHostToDevice));
             }
             if (c.p.track_peak) {
-                CHK(dalloc(&d.peak, c.state_elems, err));
+                CHK(dalloc(&d.peak, c.state_elems + kRowPad, err));
                 CHK(dalloc(&c.peak_tmp, c.state_elems, err));
                 HIPCHK(hipMemsetAsync(d.peak, 0, c.state_elems * sizeof(T), st));
             } else {
