@@ -67,6 +67,7 @@ template <typename T> struct CatchDev {
     // for k_marchv), strips_xa those of the adjoint's reverse step (62 x 2 cells)
     int32_t march_rows, strips_x, strips_y, strips_xa;
     int32_t wave_begin, n_waves;
+    int32_t index;            // catchment of the handle (a launch may hold some of them)
     int32_t march_order;      // wavefront order, see march_wave
     int32_t march_bands;      // order 4: bands of rows of strips, a multiple of 8
     T edge_slope[4];

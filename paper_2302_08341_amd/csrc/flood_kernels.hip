@@ -1554,7 +1554,7 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
         beside_load(r0, so);
         load_row(so, r0 + 1 < ny, a);
         if constexpr (PLAN) {
-            if (!plan_step<T>(L.plan, L.plan.pc[ci], mg, L.n_total, lane, lead, head, ms)) return;
+            if (!plan_step<T>(L.plan, L.plan.pc[C.index], mg, L.n_total, lane, lead, head, ms)) return;
         }
         if constexpr (lc) {
             const int c = lane & 3;

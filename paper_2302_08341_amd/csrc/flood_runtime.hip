@@ -405,6 +405,7 @@ template <typename T> struct Impl : ImplBase {
             d.strips_x = (c.nx + strip_w - 1) / strip_w;
             d.strips_xa = (c.nx + 62 * adj_vec<T>() - 1) / (62 * adj_vec<T>());
             d.strips_y = (c.ny + d.march_rows - 1) / d.march_rows;
+            d.index = i;
             d.wave_begin = waves;
             {
                 // order 4: enough bands that one band's bed and roughness (2 values
@@ -441,16 +442,35 @@ template <typename T> struct Impl : ImplBase {
         SL.vclamp = vclamp;
     }
 
+    // One instantiation of the row march serves catchments with land cover or without: a
+    // handle that holds both kinds steps them in two launches.
+    void launch_marchv_kind(const StepLaunch<T>& L, bool land) {
+        StepLaunch<T> K = L;
+        int waves = 0;
+        K.n_catch = 0;
+        for (int i = 0; i < L.n_catch; ++i) {
+            if ((L.c[i].cls != nullptr) != land) continue;
+            CatchDev<T>& d = K.c[K.n_catch++];
+            d = L.c[i];
+            d.wave_begin = waves;
+            waves += d.n_waves;
+        }
+        if (K.n_catch == 0) return;
+        launch_marchv<T>(K, march_nt,
+                         (land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() || K.narrow ? 0 : 4) |
+                             (L.c[0].peak ? 8 : 0),
+                         waves, st);
+    }
+
     void launch_steps(const StepLaunch<T>& L) {
-        if (variant == 3 && !L.recompute)
-            launch_marchv<T>(L, march_nt,
-                             (any_land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() || L.narrow ? 0 : 4) |
-                                 (L.c[0].peak ? 8 : 0),
-                             total_waves, st);
-        else if (variant == 2 && !L.recompute)
+        if (variant == 3 && !L.recompute) {
+            launch_marchv_kind(L, false);
+            if (any_land) launch_marchv_kind(L, true);
+        } else if (variant == 2 && !L.recompute) {
             launch_march<T>(L, march_seg, total_waves, st);
-        else
+        } else {
             launch_step_mi<T>(mi, L, st);
+        }
     }
 
     bool vector_ok() const {
