@@ -1129,7 +1129,8 @@ __global__ __launch_bounds__(kBlock) void k_march(const StepLaunch<T> L) {
 // clamped depth stored as -0, no ledger).  REC = 2: the adjoint's recording
 // forward, the same blocks and marks with the plain step's ledger, depth-maximum
 // bins and outflow.  EXT: bit 0 land cover, bit 1 inflow links, bit 2 nx not a
-// multiple of V (neither of the former), bit 3 running maximum.
+// multiple of V (neither of the former), bit 3 running maximum (of the catchments
+// that keep one).
 constexpr int kMarchLand = 1, kMarchInflow = 2, kMarchRagged = 4, kMarchPeak = 8;
 
 // what a row of a strip needs from memory: its links, and the depth, bed and
@@ -1375,7 +1376,12 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
         CLS.set(C.cls, (uint32_t)plane);
     else
         NM.set(C.n, bytes);
-    if constexpr (PEAK) PK.set(C.peak + (size_t)k * plane, bytes);
+    // a catchment that keeps no maxima has an empty array: the range check drops the
+    // accesses, whose whole offset is the lane's
+    if constexpr (PEAK) {
+        const bool kept = C.peak != nullptr;
+        PK.set(kept ? C.peak + (size_t)k * plane : C.h[0], kept ? bytes : 0u);
+    }
     const T g = C.g, hdry = C.hdry;
     // outflow through open edges (FP64 per member and edge link); inflow links are
     // not outflow: their volume is logged by the step planner
@@ -1504,7 +1510,7 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
             m.cs = classes(sb / es);
         else
             NM.template load<V, false>(xo, sb, m.ns);
-        if constexpr (PEAK) PK.template load<V, false>(xo, so, m.pk);
+        if constexpr (PEAK) PK.template load<V, false>(beside_at(xo, so), 0, m.pk);
     };
     // first loads, in one go: the strip's first row, the row above it (or the
     // domain's north edge), the cells beside the strip, the first row's links

@@ -447,6 +447,7 @@ template <typename T> struct Impl : ImplBase {
     void launch_marchv_kind(const StepLaunch<T>& L, bool land) {
         StepLaunch<T> K = L;
         int waves = 0;
+        bool peak = false;
         K.n_catch = 0;
         for (int i = 0; i < L.n_catch; ++i) {
             if ((L.c[i].cls != nullptr) != land) continue;
@@ -454,11 +455,12 @@ template <typename T> struct Impl : ImplBase {
             d = L.c[i];
             d.wave_begin = waves;
             waves += d.n_waves;
+            peak |= d.peak != nullptr;
         }
         if (K.n_catch == 0) return;
         launch_marchv<T>(K, march_nt,
                          (land ? 1 : 0) | (any_inflow ? 2 : 0) | (vector_ok() || K.narrow ? 0 : 4) |
-                             (L.c[0].peak ? 8 : 0),
+                             (peak ? 8 : 0),
                          waves, st);
     }
 

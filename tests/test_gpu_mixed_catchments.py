@@ -65,3 +65,51 @@ def test_catchments_with_and_without_land_cover(fl, monkeypatch, plain, land, rb
         alone.step(420.0)
         _same_catchment(fl, both, i, alone, c["n_members"], peak=True)
         assert (both.ledger(i)["drain"] > 0.0).any() == kinds[i]
+
+
+class _Batch:
+    """Catchments of one handle, each with its own parameters."""
+
+    def __init__(self, fl, cats, rb, track_peak):
+        self.fl, self.cats = fl, cats
+        grids = [fl.make_grid(c["dem"], c["manning"], c["dx"], c["edge_kind"], c["edge_slope"],
+                              land_class=c.get("land_class")) for c in cats]
+        params = [fl.make_params(RAIN, real_bytes=rb, track_peak=p, class_runoff=c.get("class_runoff"),
+                                 class_drain=c.get("class_drain"), member_class_n=c.get("class_n"),
+                                 member_drain=c.get("drain")) for c, p in zip(cats, track_peak)]
+        self.h = fl.flood_create_batch(grids, params, [c["n_members"] for c in cats], [c["n_scale"] for c in cats],
+                                       [c["rain_mult"] for c in cats])
+
+    def field(self, m, w, i):
+        ny, nx = self.cats[i]["dem"].shape
+        shape = {self.fl.FIELD_QX: (ny, nx + 1), self.fl.FIELD_QY: (ny + 1, nx)}.get(w, (ny, nx))
+        return self.fl.flood_get_field(self.h, i, m, w, shape)
+
+    def ledger(self, i):
+        return self.fl.flood_get_ledger(self.h, i, self.cats[i]["n_members"])
+
+
+# ragged rows, whole vectors, and land cover beside plain catchments; few wavefronts and more
+@pytest.mark.parametrize("rb", [4, 8])
+@pytest.mark.parametrize("shapes,land", [([(21, 37, 2), (34, 65, 3)], (0, 0)), ([(300, 257, 16), (90, 1030, 16)], (0, 0)),
+                                         ([(300, 512, 8), (260, 512, 8), (250, 512, 6)], (0, 0, 0)),
+                                         ([(41, 260, 2), (38, 128, 3), (25, 64, 2)], (0, 1, 1))])
+@pytest.mark.parametrize("first", [0, 1])
+def test_maxima_of_some_catchments(fl, shapes, land, rb, first):
+    track = [(i + first) % 2 for i in range(len(shapes))]
+    cats = [_catch(*s, seed=80 + i, land=bool(k)) for i, (s, k) in enumerate(zip(shapes, land))]
+    both = _Batch(fl, cats, rb, track)
+    for t in (20.0, 45.0):
+        fl.flood_step(both.h, t)
+    for i, c in enumerate(cats):
+        alone = fl.FloodEnsemble([c], RAIN, real_bytes=rb, track_peak=bool(track[i]))
+        alone.step(20.0)
+        alone.step(45.0)
+        _same_catchment(fl, both, i, alone, c["n_members"], peak=bool(track[i]))
+        if track[i]:
+            assert both.field(0, fl.FIELD_PEAK, i).max() > 0.0
+        else:
+            with pytest.raises(fl.FloodError) as ex:
+                both.field(0, fl.FIELD_PEAK, i)
+            assert ex.value.status == fl.FLOOD_ESTATE
+    fl.flood_destroy(both.h)
