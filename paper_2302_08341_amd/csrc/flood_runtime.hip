@@ -599,6 +599,7 @@ template <typename T> struct Impl : ImplBase {
             key.ny[i] = cats[i].ny;
             key.nx[i] = cats[i].nx;
             key.members[i] = cats[i].N;
+            key.kind[i] = (grids[i].land_class && params[i].n_classes > 0 ? 1 : 0) | (params[i].n_inflow > 0 ? 2 : 0);
         }
         TuneChoice ch = tune_default(key);
         if (params[0].member_interleave) ch.mi = params[0].member_interleave;
@@ -930,7 +931,7 @@ template <typename T> struct Impl : ImplBase {
     flood_status autotune_geometry(const TuneKey& key, const flood_params* params, std::string& err) {
         adj_tiled = params[0].step_kernel == 0 && tiled_adjoint_by_shape();
         TuneChoice cached;
-        if (tune_lookup(key, mi, cached)) {
+        if (tune_lookup(key, mi, params[0].step_kernel, cached)) {
             if (!params[0].step_kernel && mi == 1 && !vector_only()) variant = cached.variant;
             if (!params[0].march_members) march_seg = cached.march_seg;
             march_order = forced_order >= 0 ? forced_order : cached.march_order;
@@ -1205,7 +1206,7 @@ template <typename T> struct Impl : ImplBase {
         // only a search over the full candidate set is remembered: a handle that
         // pinned part of the geometry measured a subset, whose best need not be
         // the best for a later handle of the same shape
-        bool free_search = !vector_only() && forced_order < 0;
+        bool free_search = forced_order < 0;
         for (int i = 0; i < n_catch; ++i)
             free_search &= params[i].tile_rows == 0 && params[i].chunks_per_block == 0 &&
                            params[i].step_kernel == 0 && params[i].march_rows == 0 &&

@@ -4,7 +4,8 @@
 // one problem shape after the first do not measure again, and optionally in a
 // file: $FLOOD_TUNE_CACHE, one line per tuned problem,
 // "<key> mi tile_rows cpb variant march_rows march_seg march_order rows_1,...,rows_n"
-// and, since strips of one cell a lane compete, " march_narrow"
+// and, since strips of one cell a lane compete, " march_narrow"; the key gives a
+// catchment as rows x columns x members, with l for land cover and i for inflow links
 // (rows_i: each catchment's rows per strip, 0 for march_rows).  Set
 // FLOOD_AUTOTUNE=0 to skip measuring and use the defaults (or the explicit
 // values given at creation).
@@ -21,8 +22,11 @@ namespace flood {
 
 static std::string key_string(const TuneKey& k, int mi) {
     std::string s = "b" + std::to_string(k.real_bytes) + "_mi" + std::to_string(mi);
-    for (int i = 0; i < k.n_catch; ++i)
+    for (int i = 0; i < k.n_catch; ++i) {
         s += "_" + std::to_string(k.ny[i]) + "x" + std::to_string(k.nx[i]) + "x" + std::to_string(k.members[i]);
+        if (k.kind[i] & 1) s += "l";
+        if (k.kind[i] & 2) s += "i";
+    }
     return s;
 }
 
@@ -33,7 +37,7 @@ TuneChoice tune_default(const TuneKey& k) {
     int maxm = 1;
     for (int i = 0; i < k.n_catch; ++i) maxm = k.members[i] > maxm ? k.members[i] : maxm;
     c.cpb = maxm < 16 ? maxm : 16;
-    c.variant = 3;      // vectorised row march (falls back to 2 when nx does not allow it)
+    c.variant = 3;      // vectorised row march, of any row length
     c.march_rows = 16;
     c.march_seg = 1;
     c.march_order = 1;
@@ -51,13 +55,13 @@ static std::map<std::string, TuneChoice>& memo() {
     return m;
 }
 
-bool tune_lookup(const TuneKey& k, int mi, TuneChoice& out) {
+bool tune_lookup(const TuneKey& k, int mi, int step_kernel, TuneChoice& out) {
     {
         std::lock_guard<std::mutex> lock(memo_mu);
         auto it = memo().find(key_string(k, mi));
         if (it != memo().end()) {
             out = it->second;
-            return true;
+            return !step_kernel || out.variant == step_kernel;
         }
     }
     const char* path = std::getenv("FLOOD_TUNE_CACHE");
@@ -87,7 +91,7 @@ bool tune_lookup(const TuneKey& k, int mi, TuneChoice& out) {
                 p = *end == ',' ? end + 1 : end;
             }
         }
-        if (want == key && sane) {
+        if (want == key && sane && (!step_kernel || d == step_kernel)) {
             out.mi = a;
             out.tile_rows = b;
             out.cpb = c;

@@ -9,13 +9,14 @@ struct TuneKey {
     int real_bytes;
     int n_catch;
     int ny[8], nx[8], members[8];
+    int kind[8];         // of a catchment: bit 0 land cover, bit 1 inflow links
 };
 
 struct TuneChoice {
     int mi = 1;          // members interleaved in the fastest index
     int tile_rows = 4;   // cell rows per 256-lane tile
     int cpb = 16;        // member chunks per workgroup
-    int variant = 1;     // 1 tiled kernel, 2 row-marching kernel
+    int variant = 1;     // 1 tiled kernel, 2 row-marching kernel, 3 vectorised row march
     int march_rows = 32; // rows per strip of the row-marching kernel
     int march_seg = 2;   // members marched together by one wavefront
     int march_order = 1; // wavefront order of the row-march kernels (0 to 4)
@@ -25,7 +26,11 @@ struct TuneChoice {
 
 TuneChoice tune_default(const TuneKey& k);
 bool tune_enabled();
-bool tune_lookup(const TuneKey& k, int mi, TuneChoice& out);
+// The choice remembered for a problem, for a handle that names step kernel
+// step_kernel (0: leaves it open): a geometry is that of the kernel it was measured
+// with, and of the extensions in the key (the row march's strips may be one cell
+// wide and one row tall for plain catchments, which no other form takes).
+bool tune_lookup(const TuneKey& k, int mi, int step_kernel, TuneChoice& out);
 void tune_store(const TuneKey& k, const TuneChoice& c);
 
 }  // namespace flood
