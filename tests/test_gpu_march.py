@@ -140,3 +140,15 @@ def test_members_that_end_at_different_times_in_narrow_strips(fl, monkeypatch, r
     cat = _catch(9, 130, 6)
     cat["rain_mult"] = np.array([0.0, 40.0, 0.1, 20.0, 5.0, 1.0])
     _same(fl, cat, 60.0, real_bytes=rb, march_rows=2)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+def test_a_short_step_at_a_block_edge_is_no_estimate(fl, rb):
+    # the first batch of 16 ends with a step of 1 ms up to the edge of a rain block; the 3 steps
+    # after it take one batch of 4, not two of 16
+    e = fl.FloodEnsemble([_catch(40, 128, 3)], RAIN, rain_interval=15.001, dt_fixed=1.0, real_bytes=rb, step_kernel=3,
+                         march_rows=8)
+    fl.flood_timing(e.h, fl.TIMING_BATCH)
+    e.step(18.0)
+    assert (e.ledger()["steps"] == 19).all()
+    assert fl.flood_get_timing(e.h)[1] == 20
