@@ -17,18 +17,6 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
-// Workgroup order of a launch: chunk 0 gives each XCD one contiguous range
-// (xcd_remap); chunk n > 0 deals runs of n consecutive workgroups to the XCDs in
-// turn, so that the whole chip works on one stretch of memory and only a run's
-// neighbours share an L2.  The last incomplete round keeps the launch order.
-__device__ __forceinline__ int xcd_order(int b, int nb, int chunk) {
-    if (chunk <= 0) return xcd_remap(b, nb);
-    if (b >= nb / (8 * chunk) * (8 * chunk)) return b;
-    const int x = b & 7, i = b >> 3;
-    const int run = i / chunk;
-    return (run * 8 + x) * chunk + (i - run * chunk);
-}
-
 __device__ __forceinline__ uint32_t to_bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ unsigned long long to_bits(double v) {
     return (unsigned long long)__double_as_longlong(v);

@@ -122,7 +122,6 @@ template <typename T> struct StepLaunch {
     int32_t total_blocks;
     int32_t n_total;          // members over all catchments
     int32_t recompute;        // 1: adjoint tape recomputation (see k_step)
-    int32_t xcd_chunk;        // workgroup order of the vectorised row march (see xcd_order)
     int32_t drain_rows;       // rows (4 or 8) that a lane's drained depth is summed over in single precision
     int32_t narrow;           // 1: strips of 64 cells, one a lane (see k_marchv)
     CatchDev<T> c[kMaxCatch];

@@ -1295,7 +1295,7 @@ __global__ __launch_bounds__(kBlock, march_occupancy<T>(EXT)) void k_marchv(cons
                    PEAK = (EXT & kMarchPeak) != 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wg = xcd_order(blockIdx.x, gridDim.x, L.xcd_chunk) * (kBlock / 64) + wave;
+    const int wg = xcd_remap(blockIdx.x, gridDim.x) * (kBlock / 64) + wave;
     // strips of one cell a lane: the depth maxima of a workgroup's wavefronts (see the end)
     constexpr bool kCombine = V == 1 && REC != 1;
     __shared__ HB wg_max[kCombine ? kBlock / 64 : 1];

@@ -75,7 +75,6 @@ template <typename T> struct Impl : ImplBase {
     int march_bands = 0;      // order 4: bands of rows of strips (multiple of 8); 0: from the L2 size
     int march_nt = 1;         // non-temporal state streams in the vectorised row-marching kernel
     bool nt_forced = false;
-    int march_xcd = 0;        // workgroup order of the vectorised row-marching kernel (see xcd_order)
     int total_waves = 0;      // waves of one row-marching launch
     int n_catch = 0, n_total = 0;
     std::vector<Cat> cats;
@@ -428,7 +427,6 @@ template <typename T> struct Impl : ImplBase {
             SL.c[i] = d;
         }
         SL.total_blocks = begin;
-        SL.xcd_chunk = march_xcd;
         total_waves = waves;
         if (!nt_forced) {
             // What a step reads and writes: where it fits the 256 MB last-level cache,
@@ -564,7 +562,6 @@ template <typename T> struct Impl : ImplBase {
             march_nt = std::atoi(nt) ? 1 : 0;
             nt_forced = true;
         }
-        if (const char* xc = std::getenv("FLOOD_MARCH_XCD")) march_xcd = std::min(4096, std::max(0, std::atoi(xc)));
         const char* ng = std::getenv("FLOOD_NO_GRAPH");
         use_graph = !(ng && ng[0] == '1');
         if (const char* gs = std::getenv("FLOOD_GRAPH_STEPS")) {   // steps per captured batch
