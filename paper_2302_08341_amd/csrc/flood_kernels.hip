@@ -1201,7 +1201,7 @@ __device__ __forceinline__ bool plan_step(const StepPlan<T>& P, const PlanCatch&
         dt = C.alpha * C.dx / sqrt(C.g * Hd);
         if (dt > C.dt_cap) dt = C.dt_cap;
     }
-    if (lead && lane == 0) P.dt_last[m] = dt;   // not cut to an event
+    const double dt_free = dt;   // not cut to an event
     const double edge = (jf + 1.0 > (double)C.n_rain) ? INFINITY : (jf + 1.0) * C.rain_interval;
     const double tev = h.t_end < edge ? h.t_end : edge;
     double tn;
@@ -1263,6 +1263,7 @@ __device__ __forceinline__ bool plan_step(const StepPlan<T>& P, const PlanCatch&
             P.steps_out[m] = h.steps + 1;
             P.par_out[m] = h.par ^ 1;
             P.fault_out[m] = 0;
+            P.dt_last[m] = dt_free;
             if (C.n_series > 0) P.vin[m] += vq * dt;
             P.vrain[m] += (double)ms.rinc * C.ncells * (C.dx * C.dx);
             if (P.dtlog) {
