@@ -87,14 +87,16 @@ typedef struct flood_params {
                                   Must agree across catchments of one handle. */
     int32_t tile_rows;         /* 0: autotune; else 1, 2, 4 or 8 cell rows per 256-lane tile */
     int32_t chunks_per_block;  /* 0: autotune; else member chunks processed by one workgroup */
-    int32_t step_kernel;       /* 0: autotune; 1: tiled kernel; 2: row-marching kernel; 3: vectorised
-                                  row-marching kernel (2 and 3 need member_interleave 1, i.e. members
-                                  stored in planes; 3 also needs nx a multiple of 4 (FP32) or 2 (FP64)) */
+    int32_t step_kernel;       /* 0: the library's choice: 3, of any nx, for members stored in planes
+                                  (member_interleave 0 or 1), else 1; 1: tiled kernel; 2: row-marching
+                                  kernel; 3: vectorised row-marching kernel (2 and 3 need member_interleave
+                                  0 or 1; asked for by number, 3 also needs nx a multiple of 4 (FP32) or 2
+                                  (FP64)) */
     int32_t march_rows;        /* 0: autotune; else rows per strip of the row-marching kernel, 1..4096 */
     int32_t march_members;     /* 0: autotune; else members marched together by one wavefront: 1, 2, 4, 8 */
     int32_t track_peak;        /* 1: keep each member's running maximum depth (ensemble products, Sec. 4.4,
                                   Figs. 15-16); costs a read and a write of one value per member-cell-step.
-                                  0: off */
+                                  0: off.  Each catchment's own */
     /* Land cover (Sec. 4.1, Table 1), used when the grid has a class map:
      * each member has its own Manning n per class (link value: mean of the two
      * cells' values; edge links: the inner cell's), the rain reaching a cell is
@@ -139,7 +141,8 @@ flood_status flood_create(const flood_grid* grid, const flood_params* params, in
 
 /* Create one handle holding n_catch catchments of possibly different sizes
  * (members_per_catch[i] members each).  Every step advances all of them in
- * one batched launch.  n_scale[i] / rain_mult[i] point to per-catchment
+ * one batched launch (in two where some have land cover and some do not).
+ * n_scale[i] / rain_mult[i] point to per-catchment
  * arrays or are NULL.  params[i].member_interleave must be equal for all i. */
 flood_status flood_create_batch(int32_t n_catch, const flood_grid* grids, const flood_params* params,
                                 const int32_t* members_per_catch, const double* const* n_scale,
@@ -219,8 +222,9 @@ flood_status flood_assimilate(flood_handle* h, int32_t catchment, int32_t n_gaug
  * member, its length and its state, in a tape: the row-march form (members in
  * planes with whole vectors of cells in every row, step kernel 3; FP32 handles
  * that leave the kernel open take the tiled form up to 2^20 member cells, and
- * beyond where strips of 256 cells would leave many lanes idle) keeps one state per member step in a pool of blocks
- * shared by the group, the tiled form ckpt_every + 1 states per member.  A
+ * beyond where strips of 256 cells would leave many lanes idle) keeps one state
+ * per member step in a pool of blocks shared by the group, the tiled form
+ * ckpt_every + 1 states per member.  A
  * segment ends when a member has taken ckpt_every steps in it (or the pool
  * could run out), or, in the row-march form, earlier where that lets the steps
  * still expected fit into one last segment; the group's states then become a
@@ -387,7 +391,8 @@ flood_status flood_get_adjoint_info(const flood_handle* h, int32_t* groups, int3
 
 /* Kernel configuration in use: member interleave, tile rows and chunks per
  * workgroup of catchment 0, the number of steps captured per graph, the step
- * kernel variant (1 tiled, 2 row-marching, 3 vectorised row-marching), its rows per strip, members per
+ * kernel variant (1 tiled, 2 row-marching, 3 vectorised row-marching, chosen by
+ * the library also where 3 cannot be asked for), its rows per strip, members per
  * wavefront and wavefront order (0-4: which of member, strip along x and row of strips runs fastest,
  * and how the rows are spread over the XCDs).  Any output may be NULL. */
 flood_status flood_get_config(const flood_handle* h, int32_t* member_interleave, int32_t* tile_rows,

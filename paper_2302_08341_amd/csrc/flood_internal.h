@@ -213,20 +213,21 @@ template <typename T> void launch_plan(const PlanLaunch<T>& P, hipStream_t s);
 template <typename T, int MI> void launch_step(const StepLaunch<T>& L, hipStream_t s);
 template <typename T> void launch_step_mi(int mi, const StepLaunch<T>& L, hipStream_t s);
 template <typename T> void launch_march(const StepLaunch<T>& L, int seg, int total_waves, hipStream_t s);
-// cells per lane of the vectorised row-marching kernel (nx must be a multiple of it)
 // elements that an array of rows is allocated beyond its last one: a lane of the row
 // march loads a whole vector of cells, up to three of them past the end of its row
 constexpr size_t kRowPad = 4;
+// cells per lane of the vectorised row-marching kernel in strips of whole vectors (any
+// row length: the last lane of a row may own fewer)
 template <typename T> constexpr int march_vec() { return sizeof(T) == 4 ? 4 : 2; }
 // Cells per lane of the adjoint's reverse row march, in both precisions: with
-// four FP32 cells per lane the reverse step needs 138 VGPRs (3 waves per SIMD),
-// with two 85 (5 waves per SIMD), and runs faster.
+// four FP32 cells per lane the reverse step had 138 VGPRs (3 waves per SIMD), with two
+// it has 101 (4 waves per SIMD; FP64 202 and 2), and runs faster.
 template <typename T> constexpr int adj_vec() { return 2; }
 template <typename T>
 void launch_marchv(const StepLaunch<T>& L, int nt, int ext, int total_waves, hipStream_t s);
-// wavefronts of a row-march launch over one catchment: strips x member units,
-// units padded to a multiple of four in wavefront order 2
-// wavefronts of one row-march launch over a catchment (see march_wave)
+// wavefronts of one row-march launch over a catchment: strips x member units, units
+// padded to a multiple of four in wavefront order 2, rows of strips to whole bands in
+// order 4 (see march_wave)
 inline int march_waves(int strips_x, int strips_y, int units, int order, int bands = 8) {
     if (order == 2) return strips_x * strips_y * ((units + 3) / 4 * 4);
     if (order == 4) return strips_x * ((strips_y + bands - 1) / bands * bands) * units;

@@ -67,7 +67,7 @@ template <typename T> struct Impl : ImplBase {
     hipStream_t st = nullptr;
     hipStream_t own_stream = nullptr;  // created when the caller passes the null stream
     int mi = 1;
-    int variant = 1;          // 1 tiled step kernel, 2 row-marching step kernel (mi == 1)
+    int variant = 1;          // 1 tiled step kernel; mi == 1: 2 row march, 3 vectorised row march
     int march_seg = 2;        // members per wavefront of the row-marching kernel
     int march_order = 1;      // wavefront order of the row-marching kernel
     int march_narrow = -1;    // strips of one cell a lane in the vectorised row march: as measured, -1 by rule
@@ -333,14 +333,18 @@ template <typename T> struct Impl : ImplBase {
     // wavefronts are shorter chains of arithmetic, and in FP32 no lanes idle beside a
     // narrow grid.  A step in FP32: 97 x 83 x 5 7.2 us from 10.5, 128 x 128 x 4 7.2 from 9.1, 512 x
     // 512 x 2 9.9 from 12.5, 256 x 256 x 16 13.4 from 12.7; in FP64 128 x 128 x 4 7.6 from 9.4,
-    // 256 x 256 x 4 10.2 from 10.2.  By rule where nothing is measured; else both compete.
+    // 256 x 256 x 4 10.2 from 10.2.  By rule where nothing is measured; else both compete,
+    // but for small FP32 ensembles (below).
     static size_t wide_pairs(int ny, int nx, int members) {
         const int w = 64 * march_vec<T>();
         return (size_t)((nx + w - 1) / w) * ((ny + 1) / 2) * members;
     }
     static bool narrow_pays(size_t pairs) { return pairs < (sizeof(T) == 4 ? 1024 : 512); }
     bool narrow_ok() const { return mi == 1 && !any_land && !any_inflow; }
-    // FP32 ensembles of up to 2^20 member cells: always in narrow strips
+    // FP32 ensembles of up to 2^20 member cells: always in narrow strips, whose clamp ledger
+    // adds in double as that of the tiled kernel does, which stepped them before.  At the
+    // top of that range wide strips are the faster ones (256 x 256 x 16, above), and passed
+    // over all the same.
     bool small_fp32() const {
         size_t cells = 0;
         for (const Cat& c : cats) cells += (size_t)c.ny * c.nx * c.N;
@@ -2584,7 +2588,7 @@ flood_status Impl<T>::adjoint(int c, double t_end, double sample_dt, int K, cons
             // the depth does); a margin, and ending one more segment early where it was
             // short, keep an estimate that fails as good as the full segments.  At
             // 1024 x 1024 x 16, 102 steps in segments of 100: 9 steps recomputed, not 96, and the
-            // call takes 25.0 ms, not 29.7.
+            // call takes 25.0 ms, not 29.7 (with 99 steps there is one segment either way).
             // A segment holds ckpt_every steps, or what is left for every member in the
             // pool, in whole batches.
             const int cap = (int)std::min<size_t>((size_t)ckpt_every, (pool - Gg) / Gg / B * B);
