@@ -373,19 +373,16 @@ template <typename T> struct Impl : ImplBase {
         return wide > slim * (cells < 2.6e6 && long_rows ? 1.4 : cells < 4.2e6 ? 1.04 : 1.02);
     }
 
-    // Rows that a lane's drained depth is summed over in single precision: 4 up to 14
-    // million member cells, 8 beyond.  The sum ends where a strip does, so it was once as
-    // exact as the strip height taken: over 65 shapes of 3.7 to 54 million member cells a
-    // free choice took 4 rows at half of those up to 12.2 million and at none of the 27
-    // larger ones.  The drained volume is off by 0.8 to 1.3e-8 with 4 rows, by 1.9 to 2.4e-8
-    // with 8 (against FP64 sums of the same depths).  Heights are multiples of these rows.
-    static constexpr double kDrainCells = 1.4e7;
+    static constexpr double kDrainCells = 4.5e6;
 
     // tile / grouping geometry of every catchment and the launch descriptor
     void layout_launch() {
         int begin = 0, waves = 0;
         SL.n_catch = n_catch;
         SL.n_total = n_total;
+        // the drained volume's single-precision partial sums are those of the strip height
+        // that land cover has been measured the fastest at: 4 rows up to 4.5 million member
+        // cells (27 shapes of 27), mostly 8 beyond
         double all_cells = 0.0;
         for (const Cat& c : cats) all_cells += (double)c.ny * c.nx * c.N;
         SL.drain_rows = all_cells <= kDrainCells ? 4 : 8;
@@ -1142,9 +1139,9 @@ template <typename T> struct Impl : ImplBase {
         // refined in turn (the others held), timing the whole batched launch; a
         // change is kept only when it is more than 1 % faster
         if (n_catch > 1 && variant >= 2) {
-            std::vector<int> rows_set = {4, 8, 16, 32, 64};
-            if (variant != 3 || (any_land && SL.drain_rows == 8)) rows_set.erase(rows_set.begin());
-            if (variant != 3) rows_set.push_back(128);
+            const std::vector<int> rows_set = any_land       ? std::vector<int>{8, 16, 32, 64}
+                                              : variant == 3 ? std::vector<int>{4, 8, 16, 32, 64}
+                                                           : std::vector<int>{8, 16, 32, 64, 128};
             auto time_layout = [&](float* out) -> flood_status {
                 layout_launch();
                 launch_steps(SL);   // warm-up
