@@ -373,6 +373,12 @@ template <typename T> struct Impl : ImplBase {
         return wide > slim * (cells < 2.6e6 && long_rows ? 1.4 : cells < 4.2e6 ? 1.04 : 1.02);
     }
 
+    // Rows that a lane's drained depth is summed over in single precision: 4 up to 4.5
+    // million member cells, 8 beyond.  The sum once ended where a strip did; of 65 shapes of
+    // 3.7 to 54 million member cells a free choice took strips of 4 rows at six of the nine up
+    // to 4.5 million, at 12 of the 32 from there to 12.2 million and at none of the 24 beyond.
+    // The drained volume is off by 0.8 to 1.3e-8 with 4 rows and by 1.9 to 2.4e-8 with 8
+    // (against FP64 sums of the same depths).
     static constexpr double kDrainCells = 4.5e6;
 
     // tile / grouping geometry of every catchment and the launch descriptor
@@ -380,9 +386,6 @@ template <typename T> struct Impl : ImplBase {
         int begin = 0, waves = 0;
         SL.n_catch = n_catch;
         SL.n_total = n_total;
-        // the drained volume's single-precision partial sums are those of the strip height
-        // that land cover has been measured the fastest at: 4 rows up to 4.5 million member
-        // cells (27 shapes of 27), mostly 8 beyond
         double all_cells = 0.0;
         for (const Cat& c : cats) all_cells += (double)c.ny * c.nx * c.N;
         SL.drain_rows = all_cells <= kDrainCells ? 4 : 8;
@@ -1029,11 +1032,7 @@ template <typename T> struct Impl : ImplBase {
                         cands.push_back({2, cats[0].tile_rows, cats[0].cpb, mr, sg, od});
         }
         if (want3) {
-            // strips of 2 rows pay where a launch has too few wavefronts for the chip
-            // otherwise; with land cover heights are multiples of the rows that the drained
-            // volume is summed by
-            std::vector<int> heights = {2, 4, 8, 16, 32, 64};
-            if (any_land) heights.erase(heights.begin(), heights.begin() + (SL.drain_rows == 4 ? 1 : 2));
+            const std::vector<int> heights = strip_heights(any_land ? SL.drain_rows : 0, false);
             for (int od : {0, 1, 2, 3, 4})
                 if ((forced_order < 0 || od == forced_order) && !(narrow_ok() && small_fp32()))
                     for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 0});
@@ -1139,8 +1138,7 @@ template <typename T> struct Impl : ImplBase {
         // refined in turn (the others held), timing the whole batched launch; a
         // change is kept only when it is more than 1 % faster
         if (n_catch > 1 && variant >= 2) {
-            const std::vector<int> rows_set = any_land       ? std::vector<int>{8, 16, 32, 64}
-                                              : variant == 3 ? std::vector<int>{4, 8, 16, 32, 64}
+            const std::vector<int> rows_set = variant == 3 ? strip_heights(any_land ? SL.drain_rows : 0, true)
                                                            : std::vector<int>{8, 16, 32, 64, 128};
             auto time_layout = [&](float* out) -> flood_status {
                 layout_launch();

@@ -44,6 +44,14 @@ TuneChoice tune_default(const TuneKey& k) {
     return c;
 }
 
+std::vector<int> strip_heights(int drain_rows, bool refine) {
+    // strips of 2 rows pay where a launch has too few wavefronts for the chip otherwise
+    std::vector<int> h;
+    for (int r : {2, 4, 8, 16, 32, 64})
+        if (r >= (refine ? 4 : 2) && (drain_rows == 0 || r % drain_rows == 0)) h.push_back(r);
+    return h;
+}
+
 bool tune_enabled() {
     const char* e = std::getenv("FLOOD_AUTOTUNE");
     return !(e && e[0] == '0');

@@ -3,6 +3,8 @@
 // text cache of measured choices.
 #pragma once
 
+#include <vector>
+
 namespace flood {
 
 struct TuneKey {
@@ -25,6 +27,11 @@ struct TuneChoice {
 };
 
 TuneChoice tune_default(const TuneKey& k);
+// Strip heights that the vectorised row march is tried at, and again for each of
+// several catchments (refine).  drain_rows: with land cover, the rows that the drained
+// volume is summed over (0: none); its strips are whole numbers of them, so that the
+// sum is the same for every height.
+std::vector<int> strip_heights(int drain_rows, bool refine);
 bool tune_enabled();
 // The choice remembered for a problem, for a handle that names step kernel
 // step_kernel (0: leaves it open): a geometry is that of the kernel it was measured

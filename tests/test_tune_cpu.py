@@ -89,3 +89,19 @@ def test_the_same_from_a_file(tmp_path):
     f.unlink()
     assert _run(tmp_path, SRC, FLOOD_TUNE_CACHE=str(f)).returncode == 0
     assert f.read_text().count("\n") == 2
+
+
+def test_strip_heights(tmp_path):
+    r = _run(tmp_path, r"""
+#include "flood_tune.h"
+using flood::strip_heights;
+using V = std::vector<int>;
+int main() {
+    if (strip_heights(0, false) != V{2, 4, 8, 16, 32, 64} || strip_heights(0, true) != V{4, 8, 16, 32, 64}) return 1;
+    // with land cover from the rows of the drained volume's sums on, each catchment's too
+    for (bool refine : {false, true})
+        if (strip_heights(4, refine) != V{4, 8, 16, 32, 64} || strip_heights(8, refine) != V{8, 16, 32, 64}) return 2;
+    return 0;
+}
+""")
+    assert r.returncode == 0, r.returncode
