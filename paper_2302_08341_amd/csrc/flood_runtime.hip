@@ -333,8 +333,8 @@ template <typename T> struct Impl : ImplBase {
     // wavefronts are shorter chains of arithmetic, and in FP32 no lanes idle beside a
     // narrow grid.  A step in FP32: 97 x 83 x 5 7.2 us from 10.5, 128 x 128 x 4 7.2 from 9.1, 512 x
     // 512 x 2 9.9 from 12.5, 256 x 256 x 16 13.4 from 12.7; in FP64 128 x 128 x 4 7.6 from 9.4,
-    // 256 x 256 x 4 10.2 from 10.2.  By rule where nothing is measured; else both compete,
-    // but for small FP32 ensembles (below).
+    // 256 x 256 x 4 10.2 from 10.2.  By rule where nothing is measured; else both compete
+    // (narrow_competes), but for small FP32 ensembles (below).
     static size_t wide_pairs(int ny, int nx, int members) {
         const int w = 64 * march_vec<T>();
         return (size_t)((nx + w - 1) / w) * ((ny + 1) / 2) * members;
@@ -1036,10 +1036,7 @@ template <typename T> struct Impl : ImplBase {
             for (int od : {0, 1, 2, 3, 4})
                 if ((forced_order < 0 || od == forced_order) && !(narrow_ok() && small_fp32()))
                     for (int mr : heights) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 0});
-            // strips of one cell a lane compete while the chip holds all the others' wavefronts
-            size_t pairs = 0;
-            for (const Cat& c : cats) pairs += wide_pairs(c.ny, c.nx, c.N);
-            if (narrow_ok() && pairs <= 8192)
+            if (narrow_ok() && narrow_competes(key))
                 for (int od : {0, 1, 2, 3, 4})
                     if (forced_order < 0 || od == forced_order)
                         for (int mr : {1, 2, 4, 8, 16}) cands.push_back({3, cats[0].tile_rows, cats[0].cpb, mr, 1, od, 1});

@@ -52,6 +52,18 @@ std::vector<int> strip_heights(int drain_rows, bool refine) {
     return h;
 }
 
+bool narrow_competes(const TuneKey& k) {
+    const int w = 64 * 16 / k.real_bytes;
+    double pairs = 0.0, lanes = 0.0, cells = 0.0;
+    for (int i = 0; i < k.n_catch; ++i) {
+        const double strips = (k.nx[i] + w - 1) / w, rows = (double)k.ny[i] * k.members[i];
+        pairs += strips * ((k.ny[i] + 1) / 2) * k.members[i];
+        lanes += strips * w * rows;
+        cells += k.nx[i] * rows;
+    }
+    return pairs <= 8192.0 || lanes > 1.25 * cells;
+}
+
 bool tune_enabled() {
     const char* e = std::getenv("FLOOD_AUTOTUNE");
     return !(e && e[0] == '0');

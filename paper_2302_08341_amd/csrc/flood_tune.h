@@ -32,6 +32,15 @@ TuneChoice tune_default(const TuneKey& k);
 // volume is summed over (0: none); its strips are whole numbers of them, so that the
 // sum is the same for every height.
 std::vector<int> strip_heights(int drain_rows, bool refine);
+// Whether strips of one cell a lane compete with those of whole vectors (16 bytes of
+// cells a lane) for plain catchments: while the chip holds all the wavefronts of the
+// latter, two rows tall, and where these leave more than a fifth of their lanes idle
+// beside the grid.  A pass over 60 s in FP32, vectors against one cell a lane, ms: 40
+// members of 1000 x 48 3.32 and 1.66, 1000 x 97 3.80 and 2.56, 1000 x 128 3.58 and 2.62, 1000 x
+// 160 3.79 and 3.69, 1000 x 192 (three quarters of the lanes in use) 3.71 and 3.57; 300 x 301
+// x 96 5.47 and 4.21.  A step of 1000 x 224 x 40 (seven eighths) 40 and 44 us: from there on
+// one cell a lane pays on few wavefronts only.
+bool narrow_competes(const TuneKey& k);
 bool tune_enabled();
 // The choice remembered for a problem, for a handle that names step kernel
 // step_kernel (0: leaves it open): a geometry is that of the kernel it was measured

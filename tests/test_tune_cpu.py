@@ -105,3 +105,29 @@ int main() {
 }
 """)
     assert r.returncode == 0, r.returncode
+
+
+def test_where_strips_of_one_cell_a_lane_compete(tmp_path):
+    r = _run(tmp_path, r"""
+#include "flood_tune.h"
+using namespace flood;
+static bool competes(int rb, int ny, int nx, int n) {
+    TuneKey k{};
+    k.real_bytes = rb;
+    k.n_catch = 1;
+    k.ny[0] = ny, k.nx[0] = nx, k.members[0] = n;
+    return narrow_competes(k);
+}
+int main() {
+    // few wavefronts
+    if (!competes(4, 97, 83, 5) || !competes(4, 128, 256, 128) || !competes(8, 256, 128, 64)) return 1;
+    // many, on grids that leave lanes idle: rows shorter than a strip, or just past one
+    if (!competes(4, 1000, 48, 40) || !competes(4, 1000, 128, 40) || !competes(4, 300, 301, 96)) return 2;
+    if (!competes(8, 1000, 64, 40) || !competes(4, 4096, 1, 1024)) return 3;
+    // many, with the lanes in use
+    if (competes(4, 1000, 256, 40) || competes(4, 2000, 2000, 96) || competes(4, 1000, 224, 40)) return 4;
+    if (competes(8, 1000, 128, 40) || competes(4, 701, 503, 96)) return 5;
+    return 0;
+}
+""")
+    assert r.returncode == 0, r.returncode
