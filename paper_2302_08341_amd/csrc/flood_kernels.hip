@@ -1283,7 +1283,7 @@ __device__ __forceinline__ bool plan_step(const StepPlan<T>& P, const PlanCatch&
 // V: cells per lane, 16 bytes of them, or one.  With one a strip is 64 cells wide: small
 // grids, bound by the chain of a wavefront's arithmetic (0.35 us a row against 1.3 us)
 // and by lanes that idle beside a row shorter than 256 cells, get more and shorter ones
-// (97 x 83 x 5 in FP32 7.2 us a step from 10.5; see narrow_pays for where the line lies).
+// (97 x 83 x 5 in FP32 7.2 us a step from 10.5; see narrow_pays and narrow_competes for where the line lies).
 // Wavefronts per SIMD the registers are budgeted for: four in FP32 (128 registers; three
 // where inflow links meet another extension and four would spill), two in FP64.
 template <typename T> constexpr int march_occupancy(int ext) {
